@@ -150,6 +150,14 @@ struct TailDev {
   int64_t capacity;
 };
 
+// markers left to the FP64 kernel, per panel: rows (within the marker block)
+// at entries[j * stride + k], k < count[j]
+struct RedoDev {
+  int32_t* entries;
+  uint32_t* count;
+  int64_t stride;
+};
+
 struct GemmArgs {
   const uint8_t* geno;
   int64_t row_bytes;
@@ -174,6 +182,12 @@ struct GemmArgs {
   TailDev tail;
   HitDev hits;
   int64_t m_begin;   // absolute index of output row 0
+  // small tiles that form Q^T g beside the tests:
+  const MarkerStat* mstat;
+  float wscale;      // undoes the operand scale of the Q columns
+  int32_t lo_slot;   // the last slot carries c - c8
+  RedoDev redo;
+  int32_t lo_tile;   // small tiles, FP16 + FP8 form: the wide tile whose order of the FP8 lo step they follow
 };
 
 struct StatsArgs {
@@ -189,14 +203,6 @@ struct StatsArgs {
   uint32_t* redo_count;  // [n_panels]: zeroed by the block's first workgroup
   int32_t n_panels;
   int32_t lo_int;        // FP16 + FP8 form: the FP8 lo pass centres on the integer c8 = rint(c)
-};
-
-// markers left to the FP64 kernel, per panel: rows (within the marker block)
-// at entries[j * stride + k], k < count[j]
-struct RedoDev {
-  int32_t* entries;
-  uint32_t* count;
-  int64_t stride;
 };
 
 struct RedoArgs {
@@ -274,6 +280,16 @@ int tile_alias(int idx, int prec, bool g8 = false);  // smallest tile index that
 hipError_t launch_gemm(int idx, int prec, int mode, const GemmArgs& a, int grid, hipStream_t s, bool g8 = false);
 // precisions that 8-bit dosages run in (exact re-centred operand: FP32 and the FP16 split)
 __host__ __device__ constexpr bool g8_supported(int prec) { return prec == kFP32 || prec == kSplit16 || prec == kSplit8; }
-int wgemm_tile();  // tile shape used for the Q^T g contraction
+// small tiles (split forms): one workgroup per tile, no resident grid; nqb: packed covariate blocks formed
+// beside the tests
+TileShape small_shape(int idx);
+// the small tile of a marker block, or -1 where the plan's tile is the faster one
+int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_cu);
+// of a one-panel block whose Q^T g (nqb packed blocks) the same kernel forms, or -1
+int small_fused_shape(int prec, bool g8, int64_t nm, int n_cb, int nqb, int n_cu);
+// of the Q^T g contraction alone
+int small_q_shape(int prec, int64_t nm, int n_cb, int n_cu);
+const void* gemm_small_fp32_fn(int idx, int mode, bool g8);
+hipError_t launch_gemm_small(int idx, int prec, int mode, int nqb, const GemmArgs& a, hipStream_t s, bool g8);
 
 }  // namespace tgw

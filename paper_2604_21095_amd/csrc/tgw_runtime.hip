@@ -220,7 +220,6 @@ struct tgw_plan {
   HitDev hits{};  // thresholded hit list of the following scans (entries NULL: off)
   int tile = 0;
   std::vector<int> grid_main;  // per tile shape
-  int grid_w = 0;
   int w_mode = kRaw;  // kRawHL for the split forms (packed hi|lo covariate operand)
   int n_cb_w = 0;     // column blocks of the Q^T g contraction
   // 8-bit dosage rows (the FP32 and FP16 split forms): own tile choice and grids
@@ -229,7 +228,6 @@ struct tgw_plan {
   // the integer rint(c), its shift removed through the last correction slot
   bool lo_int = false;
   std::vector<int> grid_main8;
-  int grid_w8 = 0;
   bool profile = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_events;
 };
@@ -662,10 +660,8 @@ extern "C" tgw_status tgw_plan_create(const tgw_panel* const* panels, int32_t n_
     return hip_fail(e, "tgw_plan_create");
   }
   for (int i = 0; i < n_tile_shapes(); ++i) pl->grid_main.push_back(gemm_grid(i, pl->prec, kTest, pl->n_cu));
-  pl->grid_w = gemm_grid(wgemm_tile(), wprec(pl->prec), pl->w_mode, pl->n_cu);
   if (g8_supported(pl->prec)) {
     for (int i = 0; i < n_tile_shapes(); ++i) pl->grid_main8.push_back(gemm_grid(i, pl->prec, kTest, pl->n_cu, true));
-    pl->grid_w8 = gemm_grid(wgemm_tile(), wprec(pl->prec), pl->w_mode, pl->n_cu, true);
     if (o.tile < 0) {
       auto cache8 = tune_cache_read();
       auto it8 = cache8.find(tune_key(pl) + "/g8");
@@ -752,8 +748,25 @@ static GemmArgs base_args(const tgw_plan* pl, const ScanCall& c, int64_t m0, int
   return a;
 }
 
+// how the main kernel runs a marker block: the small tile shape (< 0: the
+// plan's tile), and whether it also forms Q^T g
+struct MainPath {
+  int small = -1;
+  bool fused = false;
+};
+static MainPath main_path(const tgw_plan* pl, int code, int64_t nm) {
+  const bool g8 = code == TGW_CODE_DOSAGE8;
+  MainPath p;
+  const int nqb = pl->n_panels == 1 && pl->w_mode == kRawHL ? hl_blocks(pl->panels[0]->cov->q) : 0;
+  p.small = small_fused_shape(pl->prec, g8, nm, pl->n_cb, nqb, pl->n_cu);
+  p.fused = p.small >= 0;
+  if (!p.fused) p.small = small_test_shape(pl->prec, g8, nm, pl->n_cb, pl->n_cu);
+  return p;
+}
+
 // per-block preamble: integer stats, Q^T g, ||g_res||
-static hipError_t enqueue_block_stats(tgw_plan* pl, const ScanCall& c, int64_t m0, int64_t nm, hipStream_t s) {
+static hipError_t enqueue_block_stats(tgw_plan* pl, const ScanCall& c, int64_t m0, int64_t nm, const MainPath& mp,
+                                      hipStream_t s) {
   StatsArgs sa{};
   sa.geno = c.geno;
   sa.row_bytes = c.row_bytes;
@@ -769,16 +782,18 @@ static hipError_t enqueue_block_stats(tgw_plan* pl, const ScanCall& c, int64_t m
   sa.lo_int = pl->lo_int ? 1 : 0;
   hipError_t e = launch_stats(sa, s);
   if (e != hipSuccess) return e;
+  if (mp.fused) return hipSuccess;  // the main kernel forms Q^T g and ||g_res|| itself
   GemmArgs a = base_args(pl, c, m0, nm);
-  const TileShape ws = tile_shape(wgemm_tile());
+  const bool g8 = c.code == TGW_CODE_DOSAGE8;
+  const int shape = small_q_shape(pl->prec, nm, pl->n_cb_w, pl->n_cu);
+  const TileShape ws = small_shape(shape);
   a.cblocks = pl->d_cb_w;
   a.n_cblocks = pl->n_cb_w;
-  a.n_ctiles = (int)((pl->n_cb_w + ws.wn_frags - 1) / ws.wn_frags);
+  a.n_ctiles = pl->n_cb_w;
   a.n_mtiles = (int)((nm + ws.tm() - 1) / ws.tm());
   a.raw_out = pl->wws;
   a.raw_ld = (int64_t)pl->n_panels * kSlots;
-  const bool g8 = c.code == TGW_CODE_DOSAGE8;
-  e = launch_gemm(wgemm_tile(), wprec(pl->prec), pl->w_mode, a, g8 ? pl->grid_w8 : pl->grid_w, s, g8);
+  e = launch_gemm_small(shape, wprec(pl->prec), pl->w_mode, 1, a, s, g8);
   if (e != hipSuccess) return e;
   return launch_finalize(pl->mstat, pl->wws, pl->invh, nm, pl->n_panels,
                          f16_scaled(pl->prec) ? 1.0f / kF16Scale : 1.0f, pl->lo_int ? 1 : 0,
@@ -809,16 +824,29 @@ static hipError_t enqueue_redo(tgw_plan* pl, const ScanCall& c, int64_t m0, hipS
   return launch_redo(r, pl->n_cu, s);
 }
 
-static hipError_t enqueue_main(tgw_plan* pl, const ScanCall& c, int64_t m0, int64_t nm, int tile, hipStream_t s) {
+static hipError_t enqueue_main(tgw_plan* pl, const ScanCall& c, int64_t m0, int64_t nm, int tile, const MainPath& mp,
+                               hipStream_t s) {
   GemmArgs a = base_args(pl, c, m0, nm);
   const bool g8 = c.code == TGW_CODE_DOSAGE8;
-  const TileShape ts = tile_shape_for(tile, pl->prec, g8);
-  const int grid = g8 ? pl->grid_main8[tile] : pl->grid_main[tile];
+  const bool small = mp.small >= 0;
+  const TileShape ts = small ? small_shape(mp.small) : tile_shape_for(tile, pl->prec, g8);
   a.cblocks = pl->d_cb_main;
   a.n_cblocks = pl->n_cb;
   a.n_ctiles = (pl->n_cb + ts.wn_frags - 1) / ts.wn_frags;
   a.n_mtiles = (int)((nm + ts.tm() - 1) / ts.tm());
-  if (!pl->profile) return launch_gemm(tile, pl->prec, kTest, a, grid, s, g8);
+  a.lo_tile = tile == 1 || tile == 6 ? tile : 0;
+  if (mp.fused) {
+    a.mstat = pl->mstat;
+    a.wscale = f16_scaled(pl->prec) ? 1.0f / kF16Scale : 1.0f;
+    a.lo_slot = pl->lo_int ? 1 : 0;
+    a.redo = RedoDev{pl->redo_entries, pl->redo_count, pl->MB};
+  }
+  auto launch = [&] {
+    if (small)
+      return launch_gemm_small(mp.small, pl->prec, kTest, mp.fused ? hl_blocks(pl->panels[0]->cov->q) : 0, a, s, g8);
+    return launch_gemm(tile, pl->prec, kTest, a, g8 ? pl->grid_main8[tile] : pl->grid_main[tile], s, g8);
+  };
+  if (!pl->profile) return launch();
   hipEvent_t e0, e1;
   hipError_t e = hipEventCreate(&e0);
   if (e != hipSuccess) return e;
@@ -829,7 +857,7 @@ static hipError_t enqueue_main(tgw_plan* pl, const ScanCall& c, int64_t m0, int6
   }
   pl->prof_events.emplace_back(e0, e1);
   e = hipEventRecord(e0, s);
-  if (e == hipSuccess) e = launch_gemm(tile, pl->prec, kTest, a, grid, s, g8);
+  if (e == hipSuccess) e = launch();
   if (e == hipSuccess) e = hipEventRecord(e1, s);
   return e;
 }
@@ -860,8 +888,9 @@ hipError_t tgw::enqueue_scan_rows(tgw_plan* pl, const ScanCall& c, int64_t m_lo,
   hipError_t e = hipSuccess;
   for (int64_t m0 = m_lo; e == hipSuccess && m0 < m_hi; m0 += pl->MB) {
     const int64_t nm = std::min(pl->MB, m_hi - m0);
-    e = enqueue_block_stats(pl, c, m0, nm, s);
-    if (e == hipSuccess) e = enqueue_main(pl, c, m0, nm, c.code == TGW_CODE_DOSAGE8 ? pl->tile8 : pl->tile, s);
+    const MainPath mp = main_path(pl, c.code, nm);
+    e = enqueue_block_stats(pl, c, m0, nm, mp, s);
+    if (e == hipSuccess) e = enqueue_main(pl, c, m0, nm, c.code == TGW_CODE_DOSAGE8 ? pl->tile8 : pl->tile, mp, s);
     if (e == hipSuccess) e = enqueue_redo(pl, c, m0, s);
   }
   return e;
@@ -956,7 +985,8 @@ extern "C" tgw_status tgw_plan_autotune(tgw_plan* pl, const uint8_t* d_geno, int
   const int64_t nm = std::min(pl->MB, m_end - m_begin);
   HIP_TRY(enqueue_bind(pl, outs, s));
   HIP_TRY(launch_tail_reset(TailDev{pl->tail_entries, pl->tail_count, pl->tail_cap}, s));
-  HIP_TRY(enqueue_block_stats(pl, c, m_begin, nm, s));
+  const MainPath tiles{};  // the tile shapes themselves are timed, also where a scan would take small tiles
+  HIP_TRY(enqueue_block_stats(pl, c, m_begin, nm, tiles, s));
   const HitDev saved_hits = pl->hits;  // repeated timing runs must not append hits
   pl->hits = HitDev{};
   struct Restore {
@@ -973,11 +1003,11 @@ extern "C" tgw_status tgw_plan_autotune(tgw_plan* pl, const uint8_t* d_geno, int
   hipError_t err = hipSuccess;
   for (int t = 0; t < n_tile_shapes() && err == hipSuccess; ++t) {
     if (tile_alias(t, pl->prec, g8) != t) continue;  // same kernel as an earlier shape
-    err = enqueue_main(pl, c, m_begin, nm, t, s);  // warm-up
+    err = enqueue_main(pl, c, m_begin, nm, t, tiles, s);  // warm-up
     if (err != hipSuccess) break;
     const int reps = 3;
     err = hipEventRecord(e0, s);
-    for (int r = 0; r < reps && err == hipSuccess; ++r) err = enqueue_main(pl, c, m_begin, nm, t, s);
+    for (int r = 0; r < reps && err == hipSuccess; ++r) err = enqueue_main(pl, c, m_begin, nm, t, tiles, s);
     if (err == hipSuccess) err = hipEventRecord(e1, s);
     if (err == hipSuccess) err = hipEventSynchronize(e1);
     float ms = 0.f;
@@ -1292,10 +1322,8 @@ extern "C" tgw_status tgw_scan_static(const tgw_panel* const* panels, int32_t n_
   pl.grid_main.clear();
   pl.grid_main8.clear();
   for (int i = 0; i < n_tile_shapes(); ++i) pl.grid_main.push_back(gemm_grid(i, prec, kTest, n_cu));
-  pl.grid_w = gemm_grid(wgemm_tile(), wprec(prec), pl.w_mode, n_cu);
   if (g8_supported(prec)) {
     for (int i = 0; i < n_tile_shapes(); ++i) pl.grid_main8.push_back(gemm_grid(i, prec, kTest, n_cu, true));
-    pl.grid_w8 = gemm_grid(wgemm_tile(), wprec(prec), pl.w_mode, n_cu, true);
   }
 
   ScanCall c{d_geno, n_markers, row_bytes, (int)code, m_begin, m_end, outs, 0};

@@ -1,0 +1,610 @@
+// The contraction on small tiles: scans whose 512 x 128 tiles would leave
+// most of the GPU idle (few markers, or a panel of a few columns), and the
+// Q^T g contraction of the split forms.
+#include "tgw_device.h"
+
+namespace tgw {
+
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
+// ---------------------------------------------------------------------------
+// One workgroup per tile: 4 waves of WMF 32-row fragments across WN column
+// blocks of phenotypes and NQB packed hi|lo blocks of covariates.
+//   MODE kTest,  NQB = 0: the scan's tests, Q^T g from a.wws / a.invh
+//   MODE kTest,  NQB > 0: one panel whose columns fit in one tile: Q^T g, the
+//                         markers' ||g_res|| and the tests in one pass
+//   MODE kRawHL, WN = 0:  Q^T g alone (slots to a.raw_out)
+// Every accumulator takes the same matrix-core steps in the same order as in
+// the wide kernel (chunk by chunk; within a chunk the four K16 steps, the FP8
+// lo step at the place the wide tile a.lo_tile gives it), so a test's bits do
+// not depend on the tile that computed it.
+//
+// Rows: a lane pair (h = 0, 1) of a fragment row reads eight chunks (one
+// 128-byte run of the row) at a time, 64 bytes per lane, and swaps halves
+// with v_permlane32_swap, so that each lane ends up with its half of every
+// chunk; the next eight chunks are requested a whole group ahead.  (8-bit
+// dosages: a lane reads its own 32 bytes of a chunk, two chunks at a time.)
+// Operand: staged through LDS, CS chunks per stage, two stages, the stage
+// after the next one in registers; one barrier per stage.  Chunks past the
+// last one are staged as zeros, which leave the accumulators as they are.
+// The decode (56 VALU instructions per fragment and chunk in the FP16 + FP8
+// form, about the issue time of the matrix-core steps against one column
+// block) runs a step ahead of the matrix-core instructions it feeds.
+// ---------------------------------------------------------------------------
+template <int PREC, int MODE, int WMF, int WN, int NQB, bool G8>
+__global__ __launch_bounds__(256, 2) void gemm_small_kernel(GemmArgs a) {
+  constexpr int NW = 4, NT = NW * 64, TM = NW * WMF * 32;
+  constexpr bool HL = MODE == kRawHL;
+  constexpr bool F8 = PREC == kSplit8;
+  constexpr bool LO16 = !F8;
+  constexpr bool FUSED = MODE == kTest && NQB > 0;
+  static_assert(PREC != kFP32 && MODE != kRaw && (HL ? (WN == 0 && NQB == 1) : WN >= 1), "split forms");
+  static_assert(!G8 || PREC != kSplit, "8-bit dosages run the FP16 forms");
+  constexpr int SB = block_bytes(PREC);      // bytes of a phenotype block's chunk
+  constexpr int QB = kBlockBytes / 2;        // used bytes of a packed covariate block's chunk
+  constexpr int CHB = WN * SB + NQB * QB;    // staged bytes per chunk
+  constexpr int CS = 8 * CHB <= 80 * 1024 ? 4 : 4 * CHB <= 80 * 1024 ? 2 : 1;
+  constexpr int STG = CS * CHB;
+  constexpr int NQ = STG / (NT * 16);
+  constexpr int PPF = CS * SB / 1024, PPC = SB / 1024;  // 1 KiB pieces per phenotype block and stage, per chunk
+  constexpr int QPF = CS * QB / 1024, QPC = QB / 1024;
+  constexpr int GCH = 8;                     // chunks per unrolled group
+  static_assert(STG % (NT * 16) == 0 && GCH % (2 * CS) == 0, "stage shape");
+  constexpr int QOFF = WN * CS * SB;         // covariate blocks within a stage
+  // epilogue: one fragment of accumulators per wave, the rows' 1/||g_res||,
+  // the p-value table, and (fused) the rows' slots
+  constexpr int WSP = kSlots + 4;            // padded slots of a row
+  constexpr int STAGE_BYTES = MODE == kTest ? NW * 32 * 32 * 4 : 0;
+  constexpr int IH_BYTES = MODE == kTest ? TM * 8 : 0;
+  constexpr int TAB_BYTES = MODE == kTest ? kTabIntervals * 16 : 0;
+  constexpr int WS_BYTES = FUSED ? TM * WSP * 4 : 0;
+  constexpr int EPI_BYTES = STAGE_BYTES + IH_BYTES + TAB_BYTES + WS_BYTES;
+  __shared__ __attribute__((aligned(16))) char smem[2 * STG > EPI_BYTES ? 2 * STG : EPI_BYTES];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 5;
+  const int r32 = lane & 31;
+  const int64_t W = (int64_t)a.n_mtiles * a.n_ctiles;
+  const int xcd = blockIdx.x & 7;
+  const int64_t wlo = W * xcd / 8, whi = W * (xcd + 1) / 8;
+  const int64_t w = wlo + (blockIdx.x >> 3);
+  if (w >= whi) return;
+  int mtile, ctile;
+  grouped_tile(w, a.n_mtiles, a.n_ctiles, mtile, ctile);
+  const int nch = a.n_chunks;
+
+  // this wave's 1 KiB pieces of a stage: source, chunk stride and chunk of each
+  const char* bsrc[NQ];
+  int bch[NQ], bstr[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int piece = q * NW + wave;
+    if (piece < WN * PPF) {
+      const int cb = ctile * WN + piece / (WN ? PPF : 1);
+      bsrc[q] = a.cblocks[cb < a.n_cblocks ? cb : ctile * WN].op + (piece % PPC) * 1024;
+      bch[q] = (piece % (WN ? PPF : 1)) / PPC;
+      bstr[q] = SB;
+    } else {
+      const int qp = piece - WN * PPF;
+      const int qb = qp / (NQB ? QPF : 1);
+      const char* wop = HL ? a.cblocks[ctile].op : (const char*)a.panels[0].wop + (int64_t)qb * nch * kBlockBytes;
+      bsrc[q] = wop + (qp % QPC) * 1024;
+      bch[q] = (qp % QPF) / QPC;
+      bstr[q] = kBlockBytes;
+    }
+  }
+  u32x4 breg[NQ];
+  const uint32_t lane16 = lane * 16;
+  auto load_stage = [&](int ch0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int ch = ch0 + bch[q] < nch ? ch0 + bch[q] : nch - 1;
+      breg[q] = gload<u32x4>(bsrc[q] + (int64_t)ch * bstr[q] + lane16);
+    }
+  };
+  auto store_stage = [&](int buf, int ch0) __attribute__((always_inline)) {
+    if (ch0 + CS > nch) {  // uniform: chunks past the last one are zero
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if (ch0 + bch[q] >= nch) breg[q] = u32x4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) *(u32x4*)(smem + buf * STG + (q * NW + wave) * 1024 + lane16) = breg[q];
+  };
+
+  const int64_t rowbase = (int64_t)mtile * TM + wave * (WMF * 32);
+  const uint8_t* ap[WMF];
+  uint2 lut[WMF];
+  uint32_t lut8[WMF];
+#pragma unroll
+  for (int fm = 0; fm < WMF; ++fm) {
+    int64_t mr = rowbase + fm * 32 + r32;
+    mr = mr < a.nm ? mr : a.nm - 1;
+    ap[fm] = a.geno + (a.m0 + mr) * a.row_bytes + (G8 ? 32 * h : 0);
+    const uint4 l4 = gload<uint4>(a.mlut + mr);
+    lut[fm] = make_uint2(l4.x, l4.y);
+    lut8[fm] = l4.z;
+  }
+  // FP8 lo step of (fragment, column block): after K16 step los[fm][fn]
+  int los[WMF][WN ? WN : 1], bscale[WN ? WN : 1];
+#pragma unroll
+  for (int fn = 0; fn < WN; ++fn) {
+    const int cb = ctile * WN + fn;
+    bscale[fn] = 127;
+    if constexpr (F8) {
+      const ColBlock blk = a.cblocks[cb < a.n_cblocks ? cb : ctile * WN];
+      if (cb < a.n_cblocks && r32 < blk.ncol) bscale[fn] = a.panels[blk.panel].lscale[blk.col0 + r32];
+    }
+#pragma unroll
+    for (int fm = 0; fm < WMF; ++fm)
+      los[fm][fn] = G8 ? 2 : a.lo_tile == 1 ? (cb & 3) : a.lo_tile == 6 ? ((cb >> 1) & 3) : ((wave * WMF + fm) & 3);
+  }
+
+  f32x16 acc[WMF][WN ? WN : 1], accq[WMF][NQB ? NQB : 1];
+#pragma unroll
+  for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+#pragma unroll
+      for (int fn = 0; fn < WN; ++fn) acc[fm][fn][i] = 0.0f;
+#pragma unroll
+      for (int fq = 0; fq < NQB; ++fq) accq[fm][fq][i] = 0.0f;
+    }
+
+  // 2-bit codes: raw[fm][i] of lane half h is chunk ch0 + 4h + i whole
+  auto load_rows = [&](int ch0, u32x4 (*dst)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if constexpr (G8) {  // 16-byte piece i & 1 of this half's bytes of chunk ch0 + (i >> 1)
+          const int ch = ch0 + (i >> 1) < nch ? ch0 + (i >> 1) : nch - 1;
+          dst[fm][i] = gload<u32x4>(ap[fm] + (int64_t)ch * 64 + 16 * (i & 1));
+        } else {
+          const int ch = ch0 + 4 * h + i < nch ? ch0 + 4 * h + i : nch - 1;
+          dst[fm][i] = gload<u32x4>(ap[fm] + (int64_t)ch * 16);
+        }
+      }
+  };
+  // then dwords 0, 1 of raw[fm][i] are this half's codes of chunk ch0 + i, and
+  // dwords 2, 3 those of chunk ch0 + 4 + i
+  auto swap_rows = [&](u32x4 (*raw)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+          const auto s = __builtin_amdgcn_permlane32_swap(raw[fm][i][d], raw[fm][i][2 + d], false, false);
+          raw[fm][i][d] = s[0];
+          raw[fm][i][2 + d] = s[1];
+        }
+  };
+  // raw[0]: the current eight chunks' rows, raw[1]: the next eight's (8-bit
+  // dosages: pairs of chunks, alternating)
+  u32x4 raw[2][WMF][4];
+  // code dword k of chunk u of the group (u = 8: the next group's first chunk)
+  auto src = [&](int u, int fm, int k) __attribute__((always_inline)) -> uint32_t {
+    if constexpr (G8) return raw[(u >> 1) & 1][fm][2 * (u & 1) + (k >> 2)][k & 3];
+    return raw[u >> 3][fm][u & 3][((u & 7) < 4 ? 0 : 2) + (k & 1)];
+  };
+
+  u32x4 A[2][WMF];                // operand of this step and the next
+  uint32_t lo4[WMF][4], hi4[WMF][4];  // operand bytes of the current code dword's sixteen samples
+  i32x8 A8[F8 ? WMF : 1], A8n[F8 && !G8 ? WMF : 1];
+  // bytes of the samples of code dword p of chunk u: low, high and FP8 bytes
+  // of samples d, d + 4, d + 8, d + 12 sit in one dword
+  auto expand = [&](int u, int p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const uint32_t y = (src(u, fm, p) >> (2 * d)) & 0x03030303u;
+        lo4[fm][d] = __builtin_amdgcn_perm(lut[fm].x, lut[fm].x, y);
+        hi4[fm][d] = __builtin_amdgcn_perm(lut[fm].y, lut[fm].y, y);
+      }
+  };
+  auto expand8 = [&](int u, int p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+      for (int d = 0; d < 4; ++d)
+        A8n[F8 && !G8 ? fm : 0][4 * p + d] =
+            (int)__builtin_amdgcn_perm(lut8[fm], lut8[fm], (src(u, fm, p) >> (2 * d)) & 0x03030303u);
+  };
+  // the operand of step j of chunk u
+  auto operand = [&](int u, int j, u32x4* dst) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fm = 0; fm < WMF; ++fm) {
+      if constexpr (!G8) {  // samples (d, d + 8) of the dword at even steps, (d + 4, d + 12) at odd ones
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+          dst[fm][d] = __builtin_amdgcn_perm(hi4[fm][d], lo4[fm][d], (j & 1) ? 0x07030501u : 0x06020400u);
+      } else {
+        const int k0 = 4 * (j >> 1) + (j & 1);
+        const uint32_t D0 = src(u, fm, k0), D1 = src(u, fm, k0 + 2);
+        const uint32_t M0 = ff_bytes(D0), M1 = ff_bytes(D1);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          const uint32_t x = __builtin_amdgcn_perm(D1, D0, 0x0c000c00u | ((4u + d) << 16) | d) | 0x64006400u;
+          const uint32_t v =
+              __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, x) + __builtin_bit_cast(f16x2, lut[fm].x));
+          const uint32_t mk = __builtin_amdgcn_perm(M1, M0, d | (d << 8) | ((4u + d) << 16) | ((4u + d) << 24));
+          dst[fm][d] = (mk & lut[fm].y) | (~mk & v);
+        }
+        if constexpr (F8) {  // as the wide kernel's cvt8
+          const int p = j >> 1;
+#pragma unroll
+          for (int d = 0; d < 4; ++d) {
+            uint32_t v = (j & 1) ? (uint32_t)A8[fm][4 * p + d] : 0u;
+            if (j & 1) {
+              v = cvt_pk_e4m3_hi(v, dst[fm][d]);
+              v = __builtin_amdgcn_perm(v, v, 0x03010200u);
+            } else {
+              v = cvt_pk_e4m3_lo(v, dst[fm][d]);
+            }
+            A8[fm][4 * p + d] = (int)v;
+          }
+        }
+      }
+    }
+  };
+  u32x4 bh[2][WN ? WN : 1], bl[2][WN ? WN : 1], bq[2][NQB ? NQB : 1];
+  auto read_b = [&](const char* stage, int c, int j, int set) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fn = 0; fn < WN; ++fn) {
+      const char* tile = stage + (fn * CS + c) * SB;
+      bh[set][fn] = *(const u32x4*)(tile + j * 1024 + lane16);
+      if constexpr (LO16) bl[set][fn] = *(const u32x4*)(tile + 4096 + j * 1024 + lane16);
+    }
+#pragma unroll
+    for (int fq = 0; fq < NQB; ++fq)
+      bq[set][fq] = *(const u32x4*)(stage + QOFF + (fq * CS + c) * QB + j * 1024 + lane16);
+  };
+
+  load_stage(0);
+  load_rows(0, raw[0]);
+  if constexpr (G8) load_rows(2, raw[1]);
+  store_stage(0, 0);
+  load_stage(CS);
+  __syncthreads();
+  if constexpr (!G8) {
+    swap_rows(raw[0]);
+    expand(0, 0);
+    if constexpr (F8) {
+      expand8(0, 0);
+      expand8(0, 1);
+    }
+  }
+  operand(0, 0, A[0]);
+  read_b(smem, 0, 0, 0);
+  for (int ch0 = 0; ch0 < nch; ch0 += GCH) {
+    if constexpr (!G8) load_rows(ch0 + GCH, raw[1]);
+#pragma unroll
+    for (int u = 0; u < GCH; ++u) {
+      const int buf = (u / CS) & 1;
+      const char* stage = smem + buf * STG;
+      if (!G8 && u == 7) swap_rows(raw[1]);
+      i32x8 B8[F8 ? WN : 1];
+      if constexpr (F8) {
+#pragma unroll
+        for (int fn = 0; fn < WN; ++fn) {
+          const char* tile = stage + (fn * CS + u % CS) * SB + 4096;
+          const u32x4 p0 = *(const u32x4*)(tile + lane16);
+          const u32x4 p1 = *(const u32x4*)(tile + 1024 + lane16);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            B8[fn][t] = (int)p0[t];
+            B8[fn][4 + t] = (int)p1[t];
+          }
+        }
+        if constexpr (!G8) {
+#pragma unroll
+          for (int fm = 0; fm < WMF; ++fm) A8[fm] = A8n[fm];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int cs = j & 1, ns = cs ^ 1;
+        if (j < 3) read_b(stage, u % CS, j + 1, ns);
+        if (j == 3) {
+          if (u % CS == CS - 1) {  // this chunk's stage is read: the next one's turn
+            store_stage(buf ^ 1, ch0 + u + 1);
+            load_stage(ch0 + u + 1 + CS);
+            __syncthreads();
+            read_b(smem + (buf ^ 1) * STG, 0, 0, ns);
+          } else {
+            read_b(stage, u % CS + 1, 0, ns);
+          }
+        }
+        // decode for the next step (and the next chunk's FP8 operand)
+        if constexpr (!G8) {
+          if (j == 1) expand(u, 1);
+          if (j == 3) expand(u + 1, 0);
+          if constexpr (F8) {
+            if (j == 0) expand8(u + 1, 0);
+            if (j == 2) expand8(u + 1, 1);
+          }
+          operand(j < 3 ? u : u + 1, (j + 1) & 3, A[ns]);
+        } else {
+          operand(j < 3 ? u : u + 1, (j + 1) & 3, A[ns]);
+          if (j == 2 && (u & 1)) load_rows(ch0 + u + 3, raw[(u >> 1) & 1]);  // this pair's codes are decoded
+        }
+#pragma unroll
+        for (int fm = 0; fm < WMF; ++fm) {
+#pragma unroll
+          for (int fq = 0; fq < NQB; ++fq) accq[fm][fq] = mfma16<PREC>(A[cs][fm], bq[cs][fq], accq[fm][fq]);
+#pragma unroll
+          for (int fn = 0; fn < WN; ++fn) acc[fm][fn] = mfma16<PREC>(A[cs][fm], bh[cs][fn], acc[fm][fn]);
+        }
+        if constexpr (LO16) {
+#pragma unroll
+          for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+            for (int fn = 0; fn < WN; ++fn) acc[fm][fn] = mfma16<PREC>(A[cs][fm], bl[cs][fn], acc[fm][fn]);
+        }
+        if constexpr (F8) {
+#pragma unroll
+          for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+            for (int fn = 0; fn < WN; ++fn)
+              if (G8 ? j == 2 : los[fm][fn] == j)
+                acc[fm][fn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A8[fm], B8[fn], acc[fm][fn], 0, 0, 0,
+                                                                              127, 0, bscale[fn]);
+        }
+      }
+    }
+    if constexpr (!G8) {
+#pragma unroll
+      for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) raw[0][fm][i] = raw[1][fm][i];
+    }
+  }
+  __syncthreads();  // all waves are done with the stages
+
+  if constexpr (HL) {
+    // slot col0 + r32, r32 < 16: hi product (column r32) plus lo product
+    // (column r32 + 16); a panel's only block also zeroes the 16 slots after
+    const ColBlock blk = a.cblocks[ctile];
+#pragma unroll
+    for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float v = accq[fm][0][i];
+        const float o = __shfl_xor(v, kHLSlots);
+        const int64_t mr = rowbase + fm * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+        if (mr < a.nm && r32 < blk.ncol)
+          gstore(a.raw_out + mr * a.raw_ld + blk.col0 + r32, r32 < kHLSlots ? v + o : 0.0f);
+      }
+  } else {
+    float cinv[WN], csp[WN];
+#pragma unroll
+    for (int fn = 0; fn < WN; ++fn) {
+      const int cb = ctile * WN + fn;
+      const ColBlock blk = a.cblocks[cb < a.n_cblocks ? cb : ctile * WN];
+      const PanelDev& pdb = a.panels[blk.panel];
+      const bool colok = cb < a.n_cblocks && r32 < blk.ncol;
+      cinv[fn] = colok ? gload<float>(pdb.invny + blk.col0 + r32) : 0.f;
+      csp[fn] = colok ? gload<float>(pdb.scale + blk.col0 + r32) * a.gunit : 0.f;
+    }
+    float* stage = (float*)smem + wave * (32 * 32);
+    float2* ihl = (float2*)(smem + STAGE_BYTES) + wave * (WMF * 32);
+    float* wsl = (float*)(smem + STAGE_BYTES + IH_BYTES + TAB_BYTES) + wave * (WMF * 32 * WSP);
+    if constexpr (FUSED) {
+      // Q^T g of this wave's rows into LDS, then one lane per row forms
+      // ||g_res|| as finalize_kernel does
+#pragma unroll
+      for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+        for (int fq = 0; fq < 2; ++fq)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            float v = 0.0f;
+            if (fq < NQB) {
+              v = accq[fm][fq < NQB ? fq : 0][i];
+              v += __shfl_xor(v, kHLSlots);
+            }
+            if (r32 < kHLSlots) wsl[(fm * 32 + 8 * (i >> 2) + 4 * h + (i & 3)) * WSP + fq * kHLSlots + r32] = v;
+          }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (lane < WMF * 32) {
+        const int64_t m = rowbase + lane;
+        ihl[lane] = finalize_row(a.mstat[m < a.nm ? m : a.nm - 1], wsl + lane * WSP, a.wscale, a.lo_slot, a.redo, 0,
+                                 m < a.nm ? (int32_t)m : -1);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    // projection correction (see gemm_kernel)
+#pragma unroll
+    for (int fn = 0; fn < WN; ++fn) {
+      const int cb = ctile * WN + fn;
+      const ColBlock blk = a.cblocks[cb < a.n_cblocks ? cb : ctile * WN];
+      const float* cwp = a.panels[blk.panel].cw + (int64_t)(blk.col0 + r32) * kSlots + 8 * h;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const float4 c0 = gload<float4>(cwp + 16 * ks);
+        const float4 c1 = gload<float4>(cwp + 16 * ks + 4);
+        const u32x4 bo = {pack_bf16x2(c0.x, c0.y), pack_bf16x2(c0.z, c0.w), pack_bf16x2(c1.x, c1.y),
+                          pack_bf16x2(c1.z, c1.w)};
+#pragma unroll
+        for (int fm = 0; fm < WMF; ++fm) {
+          tab4 w0, w1;
+          if constexpr (FUSED) {
+            const tab4* wp = (const tab4*)(wsl + (fm * 32 + r32) * WSP + 16 * ks + 8 * h);
+            w0 = wp[0];
+            w1 = wp[1];
+          } else {
+            int64_t mr = rowbase + fm * 32 + r32;
+            mr = mr < a.nm ? mr : a.nm - 1;
+            const float* wp = a.wws + (mr * a.n_panels + blk.panel) * kSlots + 16 * ks + 8 * h;
+            w0 = gload<tab4>(wp);
+            w1 = gload<tab4>(wp + 4);
+          }
+          const u32x4 ao = {pack_bf16x2(w0.x, w0.y), pack_bf16x2(w0.z, w0.w), pack_bf16x2(w1.x, w1.y),
+                            pack_bf16x2(w1.z, w1.w)};
+          acc[fm][fn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ao),
+                                                                __builtin_bit_cast(bf16x8, bo), acc[fm][fn], 0, 0, 0);
+        }
+      }
+    }
+    // 32 x 32 accumulators at a time through this wave's 4 KiB of LDS; the
+    // rows' 1/||g_res|| and the p-value table of the block's panel in LDS too
+    int panel = -1;  // whose rows and table are in LDS (uniform)
+#pragma unroll
+    for (int fn = 0; fn < WN; ++fn) {
+      const int cb = ctile * WN + fn;
+      if (cb >= a.n_cblocks) break;
+      const ColBlock blk = a.cblocks[cb];
+      if (blk.panel != panel) {
+        panel = blk.panel;
+        __syncthreads();
+        if constexpr (!FUSED) {
+          for (int k = lane; k < WMF * 32; k += 64) {
+            int64_t mr = rowbase + k;
+            mr = mr < a.nm ? mr : a.nm - 1;
+            ihl[k] = gload<float2>(a.invh + mr * a.n_panels + panel);
+          }
+        }
+        tab4* tl = (tab4*)(smem + STAGE_BYTES + IH_BYTES);
+        const tab4* tg = (const tab4*)a.panels[panel].table;
+        for (int k = tid; k < kTabIntervals; k += NT) tl[k] = gload<tab4>(tg + k);
+        __syncthreads();
+      }
+#pragma unroll
+      for (int fm = 0; fm < WMF; ++fm) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) stage[(8 * (i >> 2) + 4 * h + (i & 3)) * 32 + r32] = acc[fm][fn][i];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        finish_block<1>(stage, a, blk, rowbase + fm * 32, h, r32, (LdsTable)(smem + STAGE_BYTES + IH_BYTES),
+                        (LdsRows)(ihl + fm * 32), cinv[fn], csp[fn]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+    }
+  }
+}
+
+// {waves, fragments per wave, column blocks} of the compiled shapes
+static const TileShape kSmall[] = {{4, 1, 1}, {4, 2, 1}, {4, 1, 2}, {4, 2, 2}, {4, 1, 4}};
+constexpr int kNumSmall = sizeof(kSmall) / sizeof(kSmall[0]);
+TileShape small_shape(int idx) { return kSmall[idx]; }
+
+// Cycles (at 2.4 GHz) per 64-sample chunk of one tile, measured at N = 23,000
+// with dense outputs: alone on its CU (one tile per CU) and per tile with two
+// to four tiles per CU; `wide` is the plan's default tile.  A block takes the
+// shape with the least ceil(tiles per CU) x cycles: the wide tile computes a
+// 32 x 32 block in 390-420 cycles (FP16 + FP8) against 480-620 here, but
+// leaves CUs idle when its tiles number less than the CUs, and in its last
+// round.
+namespace {
+struct TileCost {
+  int wide, alone[kNumSmall], shared[kNumSmall];
+};
+const TileCost& tile_cost(int prec, bool g8) {
+  static const TileCost f8 = {6200, {907, 1500, 1444, 2437, 2378}, {640, 1210, 1100, 1940, 1910}};
+  static const TileCost f8_g8 = {9800, {1295, 2619, 1827, 3369, 2494}, {1190, 2220, 1555, 2950, 2230}};
+  static const TileCost f16 = {7950, {864, 1419, 1617, 2488, 2904}, {730, 1280, 1335, 2255, 2490}};
+  static const TileCost f16_g8 = {10900, {1190, 2454, 1894, 3649, 3211}, {1160, 2075, 1760, 3100, 2850}};
+  static const TileCost bf16 = {7540, {877, 1376, 1604, 2404, 2888}, {720, 1260, 1275, 2200, 2420}};
+  static const TileCost fp32 = {41900, {4803, 8678, 8113, 14292, 12862}, {3734, 7097, 6223, 11933, 10726}};
+  return prec == kSplit8 ? (g8 ? f8_g8 : f8) : prec == kSplit16 ? (g8 ? f16_g8 : f16) : prec == kSplit ? bf16 : fp32;
+}
+int64_t rounds(int64_t nm, int n_cb, const TileShape& t, int n_cu) {
+  const int64_t tiles = ((nm + t.tm() - 1) / t.tm()) * ((n_cb + t.wn_frags - 1) / t.wn_frags);
+  return (tiles + n_cu - 1) / n_cu;
+}
+}  // namespace
+
+int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_cu) {
+  const TileCost& c = tile_cost(prec, g8);
+  int64_t best = rounds(nm, n_cb, TileShape{4, 4, 4}, n_cu) * c.wide;
+  int pick = -1;
+  for (int i = 0; i < kNumSmall; ++i) {
+    const int64_t r = rounds(nm, n_cb, kSmall[i], n_cu);
+    const int64_t t = r <= 1 ? c.alone[i] : r * c.shared[i];
+    if (t < best) best = t, pick = i;
+  }
+  return pick;
+}
+
+// Q^T g beside the tests saves the second decode of the genotypes (a third
+// of the two kernels' time) and two launches; the panel's columns then have
+// to fit in one tile.  One column block and one covariate block: two
+// fragments per wave halve the operand reads (1,450 cycles per tile against
+// 2 x 830), but 256-row tiles leave more of the last round empty.
+int small_fused_shape(int prec, bool g8, int64_t nm, int n_cb, int nqb, int n_cu) {
+  if (prec == kFP32 || nqb < 1 || n_cb > 2) return -1;
+  if (n_cb == 2) return 2;
+  if (nqb > 1 || g8) return 0;
+  const int64_t r0 = rounds(nm, n_cb, kSmall[0], n_cu), r1 = rounds(nm, n_cb, kSmall[1], n_cu);
+  return r1 * (r1 > 1 ? 1450 : 1720) < r0 * (r0 > 1 ? 830 : 1000) ? 1 : 0;
+}
+
+// 256-row tiles once they fill the GPU (100,000 markers, N = 23,000: 0.21 ms
+// against 0.25 ms on 128-row ones), else 128-row ones (4,096 markers, N =
+// 500,001: 2.0 against 3.2 ms)
+int small_q_shape(int prec, int64_t nm, int n_cb, int n_cu) {
+  return prec != kFP32 && rounds(nm, n_cb, kSmall[1], n_cu) > 1 ? 1 : 0;
+}
+
+template <int PREC, int NQB, bool G8>
+static const void* small_fn(int idx) {
+  switch (idx) {
+    case 0: return (const void*)gemm_small_kernel<PREC, kTest, 1, 1, NQB, G8>;
+    case 1:
+      if constexpr (NQB < 2 && !(G8 && NQB)) return (const void*)gemm_small_kernel<PREC, kTest, 2, 1, NQB, G8>;
+      return nullptr;
+    case 2: return (const void*)gemm_small_kernel<PREC, kTest, 1, 2, NQB, G8>;
+    case 3:
+      if constexpr (NQB == 0) return (const void*)gemm_small_kernel<PREC, kTest, 2, 2, NQB, G8>;
+      return nullptr;
+    case 4:
+      if constexpr (NQB == 0) return (const void*)gemm_small_kernel<PREC, kTest, 1, 4, NQB, G8>;
+      return nullptr;
+  }
+  return nullptr;
+}
+
+template <int PREC, bool G8>
+static const void* small_fn_q(int idx, int nqb) {
+  return nqb == 0 ? small_fn<PREC, 0, G8>(idx) : nqb == 1 ? small_fn<PREC, 1, G8>(idx) : small_fn<PREC, 2, G8>(idx);
+}
+
+template <int PREC, bool G8>
+static const void* small_hl_fn(int idx) {
+  return idx == 0   ? (const void*)gemm_small_kernel<PREC, kRawHL, 1, 0, 1, G8>
+         : idx == 1 ? (const void*)gemm_small_kernel<PREC, kRawHL, 2, 0, 1, G8>
+                    : nullptr;
+}
+
+hipError_t launch_gemm_small(int idx, int prec, int mode, int nqb, const GemmArgs& a, hipStream_t s, bool g8) {
+  const void* fn = nullptr;
+  if (prec == kFP32) {
+    fn = gemm_small_fp32_fn(idx, mode, g8);
+  } else if (mode == kRawHL) {
+    if (prec == kSplit16) fn = g8 ? small_hl_fn<kSplit16, true>(idx) : small_hl_fn<kSplit16, false>(idx);
+    if (prec == kSplit && !g8) fn = small_hl_fn<kSplit, false>(idx);
+  } else if (mode == kTest) {
+    if (prec == kSplit8) fn = g8 ? small_fn_q<kSplit8, true>(idx, nqb) : small_fn_q<kSplit8, false>(idx, nqb);
+    if (prec == kSplit16) fn = g8 ? small_fn_q<kSplit16, true>(idx, nqb) : small_fn_q<kSplit16, false>(idx, nqb);
+    if (prec == kSplit && !g8) fn = small_fn_q<kSplit, false>(idx, nqb);
+  }
+  if (!fn) return hipErrorInvalidValue;
+  const int64_t tiles = (int64_t)a.n_mtiles * a.n_ctiles;
+  const int64_t grid = (tiles + 7) / 8 * 8;  // ceil(tiles / 8) workgroups per XCD's range
+  GemmArgs arg = a;
+  void* params[] = {&arg};
+  return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(256), params, 0, s);
+}
+
+}  // namespace tgw
