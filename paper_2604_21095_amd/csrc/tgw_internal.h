@@ -34,7 +34,7 @@ constexpr int kMaxPanelsPerBind = 32;
 constexpr double kRedoTol = 0.5;
 constexpr double kCollinearTol = 1e-8;
 constexpr int kRedoGroup = 16;   // listed markers per work item of the FP64 kernel
-constexpr int kRedoCols = 256;   // columns per work item (one per thread)
+constexpr int kRedoCols = 64;    // columns per work item
 
 // ---- p-value table ----------------------------------------------------------
 constexpr float kTMax = 40.0f;        // |t| beyond this goes to the FP64 tail
