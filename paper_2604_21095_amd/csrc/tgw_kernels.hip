@@ -49,12 +49,20 @@ __device__ double beta_cf(double x, double a, double b) {
   return f;
 }
 
-__device__ double ln_betai_cf(double x, double a, double b) {
-  const double lbeta = lgamma(a) + lgamma(b) - lgamma(a + b);
+// ln Gamma at a = df / 2, b = 1/2 and a + b
+struct TGamma {
+  double a, b, ab;
+};
+__device__ inline TGamma t_gamma(double df) {
+  return TGamma{lgamma(0.5 * df), lgamma(0.5), lgamma(0.5 * df + 0.5)};
+}
+
+__device__ double ln_betai_cf(double x, double a, double b, const TGamma& g) {
+  const double lbeta = g.a + g.b - g.ab;
   return a * log(x) + b * log1p(-x) - log(a) - lbeta + log(beta_cf(x, a, b));
 }
 
-__device__ double ln_p_two_sided(double t, double df) {
+__device__ double ln_p_two_sided(double t, double df, const TGamma& g) {
   t = fabs(t);
   if (isinf(t)) return -INFINITY;
   if (t == 0.0) return 0.0;
@@ -62,33 +70,33 @@ __device__ double ln_p_two_sided(double t, double df) {
   const double t2 = t * t;
   const double x = df / (df + t2);
   const double omx = t2 / (df + t2);
-  if (x < (a + 1.0) / (a + b + 2.0)) return ln_betai_cf(x, a, b);
-  return log1p(-exp(ln_betai_cf(omx, b, a)));
+  if (x < (a + 1.0) / (a + b + 2.0)) return ln_betai_cf(x, a, b, g);
+  return log1p(-exp(ln_betai_cf(omx, b, a, g)));
 }
+__device__ double ln_p_two_sided(double t, double df) { return ln_p_two_sided(t, df, t_gamma(df)); }
 
-__device__ double ln_pdf_t(double t, double df) {
-  return lgamma(0.5 * (df + 1.0)) - lgamma(0.5 * df) - 0.5 * log(df * M_PI) -
-         0.5 * (df + 1.0) * log1p(t * t / df);
-}
-
-// -log10 p of |t| and its derivative in |t|, in FP64
-__device__ void nlog10p_and_slope(double t, double df, double& f, double& fp) {
-  const double lnp = ln_p_two_sided(t, df);
-  f = -lnp / M_LN10;
-  fp = 2.0 * exp(ln_pdf_t(t, df) - lnp) / M_LN10;
+__device__ double ln_pdf_t(double t, double df, const TGamma& g) {
+  return g.ab - g.a - 0.5 * log(df * M_PI) - 0.5 * (df + 1.0) * log1p(t * t / df);
 }
 
 // the cubic Hermite interpolant of -log10 p on interval k (nodes k and k + 1,
 // values and slopes), written as its power-series coefficients in the local
-// variable s in [0, 1] so that the epilogue evaluates it with three FMAs
-__global__ void table_kernel(float4* table, double df) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= kTabIntervals) return;
-  double f0, d0, f1, d1;
-  nlog10p_and_slope((double)k / kTabPerUnit, df, f0, d0);
-  nlog10p_and_slope((double)(k + 1) / kTabPerUnit, df, f1, d1);
-  d0 /= kTabPerUnit;  // slopes per unit of s
-  d1 /= kTabPerUnit;
+// variable s in [0, 1] so that the epilogue evaluates it with three FMAs.  A
+// thread evaluates one node in FP64 (the time of the kernel is one thread's
+// continued fraction and ln Gamma calls, whose values three lanes share out);
+// neighbours exchange theirs, so a wave of 64 nodes gives 63 intervals.
+constexpr int kTabWave = 63;
+__global__ __launch_bounds__(64) void table_kernel(float4* table, double df) {
+  const int lane = threadIdx.x;
+  const double lg = lgamma(lane == 0 ? 0.5 * df : lane == 1 ? 0.5 : 0.5 * df + 0.5);
+  const TGamma g{__shfl(lg, 0), __shfl(lg, 1), __shfl(lg, 2)};
+  const int k = blockIdx.x * kTabWave + lane;
+  const double t = (double)(k < kTabNodes ? k : kTabNodes - 1) / kTabPerUnit;
+  const double lnp = ln_p_two_sided(t, df, g);
+  const double f0 = -lnp / M_LN10;
+  const double d0 = 2.0 * exp(ln_pdf_t(t, df, g) - lnp) / M_LN10 / kTabPerUnit;  // slope per unit of s
+  const double f1 = __shfl_down(f0, 1), d1 = __shfl_down(d0, 1);
+  if (lane == kTabWave || k >= kTabIntervals) return;
   table[k] = make_float4((float)f0, (float)d0, (float)(3.0 * (f1 - f0) - 2.0 * d0 - d1),
                          (float)(2.0 * (f0 - f1) + d0 + d1));
 }
@@ -464,6 +472,405 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const void* __restri
   }
 }
 
+// ---------------------------------------------------------------------------
+// phenotype preparation over sample segments (cohorts of kPrepSplitMin
+// chunks and more): the same quantities as prep_kernel, with the projections
+// on the FP64 matrix cores and the samples of 16 columns cut into S segments,
+// one wave each, so that a panel of any width fills the GPU and each element
+// of Q read serves 16 columns.  Each pass leaves its sums per segment
+// (part[slot][segment][column]) and prep_sum_kernel adds them in segment
+// order:
+//   A: sums of v = y - y_0, v^2 and Q^T v (y_0: the column's first sample,
+//      so that offsets cancel; Q^T of a constant is that constant times
+//      n Q_0 in slot 0, Q_0 being constant, and 0 in the others)
+//   B: ||y_res||^2 explicitly, only for columns that the covariates nearly
+//      explain (||y_c||^2 - ||Q^T y_c||^2 below 1e-4 ||y_c||^2, where the
+//      difference is still good to 1e-12)
+//   C: FP16 + FP8 form: the largest |lo| term
+//   D: the operand, and the sums of what it holds
+// N = 23,000, K = 10, FP16 + FP8 form: P = 2,048 (FP64 input) 1,010 -> 510 us,
+// P = 300 (K = 13) 530 -> 135 us, P = 1 333 -> 65 us; N = 500,001, P = 8: 15.2
+// -> 0.4 ms (prep_kernel before).  Bound by latency at few columns, by the
+// reads of Y (three passes of 377 MB, 3 TB/s) and FP64 issue in pass D at many.
+// ---------------------------------------------------------------------------
+struct PrepArgs {
+  const void* Y;
+  int64_t ldy, n, n_pad, P;
+  const double* Q;
+  int q, y_fp64;
+  int n_tiles, segs;      // 16-column tiles, sample segments
+  void* yop;
+  double* part;           // [slots][segs][16 n_tiles]
+  double* sums;           // [slots][16 n_tiles]: A's, then D's in the second half
+  double* r2;             // [16 n_tiles]: B
+  double* maxlo;          // [16 n_tiles]: C
+  uint8_t* lscale;
+  float* scale;
+  float* invny;
+  float* cw;
+  int32_t* flags;
+};
+constexpr int kPrepSlotV = kSlots;        // sum of v (D: sum of the operand)
+constexpr int kPrepSlotVV = kSlots + 1;   // sum of v^2 (D: its square)
+constexpr int kPrepSlotL = kSlots + 2;    // D: sum of the lo terms
+constexpr int kPrepSlots = kSlots + 3;
+
+// y at samples s0 + 4 i (s0 = first + l4) of this lane's column; zero past n
+template <bool F64>
+__device__ __forceinline__ f64x4 prep_y(const void* col, int64_t s0, int64_t n, bool whole) {
+  f64x4 v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t s = s0 + 4 * i;
+    const bool ok = whole || s < n;
+    const int64_t sc = ok ? s : 0;
+    double x;
+    if constexpr (F64)
+      x = gload<double>((const double*)col + sc);
+    else
+      x = (double)gload<float>((const float*)col + sc);
+    v[i] = ok ? x : 0.0;
+  }
+  return v;
+}
+
+// this wave's tile, segment and column
+struct PrepWave {
+  int tile, seg, l16, l4, ch_lo, ch_hi;
+  int64_t col;        // clamped to the panel
+  bool on;
+};
+__device__ __forceinline__ PrepWave prep_wave(const PrepArgs& a) {
+  PrepWave w;
+  const int lane = threadIdx.x & 63;
+  const int64_t id = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  w.on = id < (int64_t)a.n_tiles * a.segs;
+  w.tile = (int)(id % a.n_tiles);
+  w.seg = (int)(id / a.n_tiles);
+  w.l16 = lane & 15;
+  w.l4 = lane >> 4;
+  const int64_t nch = a.n_pad / kChunk;
+  w.ch_lo = (int)(nch * w.seg / a.segs);
+  w.ch_hi = (int)(nch * (w.seg + 1) / a.segs);
+  const int64_t c = (int64_t)w.tile * 16 + w.l16;
+  w.col = c < a.P ? c : a.P - 1;
+  return w;
+}
+__device__ __forceinline__ int64_t prep_at(const PrepArgs& a, int slot, int seg, int64_t c) {
+  return ((int64_t)slot * a.segs + seg) * (16 * (int64_t)a.n_tiles) + c;
+}
+// a lane's sum over its 16-sample blocks, added over the four lanes of a column
+__device__ __forceinline__ double prep_col_sum(double v) {
+  v += __shfl_xor(v, 16);
+  v += __shfl_xor(v, 32);
+  return v;
+}
+
+template <int NT, bool F64>
+__global__ __launch_bounds__(256, 4) void prep_project_kernel(PrepArgs a) {
+  const PrepWave w = prep_wave(a);
+  if (!w.on) return;
+  const char* col = (const char*)a.Y + w.col * a.ldy * (F64 ? 8 : 4);
+  const double y0 = F64 ? *(const double*)col : (double)*(const float*)col;
+  f64x4 acc[NT];
+  uint32_t oq[NT];
+#pragma unroll
+  for (int x = 0; x < NT; ++x) {
+    acc[x] = f64x4{0.0, 0.0, 0.0, 0.0};
+    oq[x] = (uint32_t)((min(16 * x + w.l16, a.q - 1) * a.n_pad + w.l4) * 8);
+  }
+  double sv = 0.0, svv = 0.0;
+  int bad = 0;
+  for (int ch = w.ch_lo; ch < w.ch_hi; ++ch) {
+    const bool whole = (int64_t)(ch + 1) * kChunk <= a.n;
+    const char* qc = (const char*)(a.Q + (int64_t)ch * kChunk);
+    // the chunk's loads are issued together
+    f64x4 y[4], qv[4][NT];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      y[b] = prep_y<F64>(col, (int64_t)ch * kChunk + 16 * b + w.l4, a.n, whole);
+#pragma unroll
+      for (int x = 0; x < NT; ++x)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qv[b][x][i] = gload<double>(qc + 128 * b + 32 * i + oq[x]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int64_t s0 = (int64_t)ch * kChunk + 16 * b + w.l4;
+      f64x4 v = y[b];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (!isfinite(v[i])) bad = 1;
+        v[i] = whole || s0 + 4 * i < a.n ? v[i] - y0 : 0.0;
+        sv += v[i];
+        svv += v[i] * v[i];
+      }
+#pragma unroll
+      for (int x = 0; x < NT; ++x)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(qv[b][x][i], v[i], acc[x], 0, 0, 0);
+    }
+  }
+  if (bad) atomicOr(a.flags, 1);
+  const int64_t c = (int64_t)w.tile * 16 + w.l16;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a.part[prep_at(a, 16 * t + 4 * i + w.l4, w.seg, c)] = acc[t][i];
+  sv = prep_col_sum(sv);
+  svv = prep_col_sum(svv);
+  if (w.l4 == 0) {
+    a.part[prep_at(a, kPrepSlotV, w.seg, c)] = sv;
+    a.part[prep_at(a, kPrepSlotVV, w.seg, c)] = svv;
+  }
+}
+
+// sums over the segments, in order: 16 columns x 16 runs of segments per
+// workgroup, each run in order and then the runs in order (MAX: the largest)
+template <bool MAX>
+__global__ __launch_bounds__(256) void prep_sum_kernel(const double* __restrict__ part, double* __restrict__ out,
+                                                       int segs, int64_t ncol) {
+  __shared__ double sh[16][17];
+  const int c = threadIdx.x & 15, r = threadIdx.x >> 4;
+  const int64_t col = (int64_t)blockIdx.x * 16 + c;
+  const double* p = part + (int64_t)blockIdx.y * segs * ncol + col;
+  const int lo = segs * r / 16, hi = segs * (r + 1) / 16;
+  double v = 0.0;
+#pragma unroll 8
+  for (int s = lo; s < hi; ++s) v = MAX ? fmax(v, p[s * ncol]) : v + p[s * ncol];
+  sh[r][c] = v;
+  __syncthreads();
+  if (r == 0) {
+    v = sh[0][c];
+#pragma unroll
+    for (int x = 1; x < 16; ++x) v = MAX ? fmax(v, sh[x][c]) : v + sh[x][c];
+    out[(int64_t)blockIdx.y * ncol + col] = v;
+  }
+}
+
+// x as a float rounded to odd (truncated, the last bit set where anything was
+// cut off): rounding that to nearest even at any width two or more bits
+// narrower gives what rounding x itself gives
+__device__ __forceinline__ float float_to_odd(double x) {
+  const float f = (float)x;
+  uint32_t u = __float_as_uint(f);
+  if (fabs((double)f) > fabs(x)) --u;
+  if ((double)f != x) u |= 1u;
+  return __uint_as_float(u);
+}
+
+// what a column's sums of pass A say
+struct PrepColumn {
+  double mean, yc2, r2;
+  bool direct;  // ||y_res||^2 from the difference of squares
+};
+__device__ __forceinline__ double prep_qty(const PrepArgs& a, int k, int64_t c, double delta) {
+  const double v = a.sums[min(k, a.q - 1) * (16 * (int64_t)a.n_tiles) + c];
+  return k == 0 ? v - delta * ((double)a.n * a.Q[0]) : k < a.q ? v : 0.0;
+}
+__device__ __forceinline__ PrepColumn prep_column(const PrepArgs& a, int64_t c, double y0, double* delta) {
+  const int64_t nc = 16 * (int64_t)a.n_tiles;
+  PrepColumn p;
+  const double d = a.sums[kPrepSlotV * nc + c] / (double)a.n;
+  p.mean = y0 + d;
+  *delta = d;
+  p.yc2 = fmax(a.sums[kPrepSlotVV * nc + c] - (double)a.n * d * d, 0.0);
+  double s = p.yc2;
+#pragma unroll 8
+  for (int k = 0; k < a.q; ++k) {
+    const double t = prep_qty(a, k, c, d);
+    s -= t * t;
+  }
+  p.r2 = s;
+  p.direct = s > 1e-4 * p.yc2;
+  return p;
+}
+
+// PASS 0: B, 1: C, 2: D; NT: 16-slot tiles of the covariate basis
+template <int PASS, int PREC, int NT, bool F64>
+__global__ __launch_bounds__(256, PASS == 2 ? 3 : 4) void prep_residual_kernel(PrepArgs a) {
+  const PrepWave w = prep_wave(a);
+  if (!w.on) return;
+  const char* colp = (const char*)a.Y + w.col * a.ldy * (F64 ? 8 : 4);
+  const double y0 = F64 ? *(const double*)colp : (double)*(const float*)colp;
+  const int64_t c = (int64_t)w.tile * 16 + w.l16;
+  double delta;
+  const PrepColumn pc = prep_column(a, c, y0, &delta);
+  if (PASS == 0 && __builtin_amdgcn_ballot_w64(!pc.direct) == 0) return;  // uniform: no column of the tile needs it
+  const double r2 = PASS == 0 || pc.direct ? pc.r2 : a.r2[c];
+  const double sp = sqrt(r2);
+  const bool valid = sp > 1e-12 * sqrt(pc.yc2);
+  const double inv = valid ? 1.0 / sp : 0.0;
+  const double inv16 = inv * (double)kF16Scale;  // a power of two times inv: v inv16 rounds as (v inv) 2^12
+  const int lsh = PASS == 2 && PREC == kSplit8 ? lo_shift(a.maxlo[c]) : 0;
+  const double lo_up = ldexp(1.0, lsh), lo_down = ldexp(1.0, -lsh);
+  constexpr int KK = 4 * NT;
+  double nq[KK];
+  uint32_t oq[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    nq[kk] = -prep_qty(a, 4 * kk + w.l4, c, delta);
+    oq[kk] = (uint32_t)((min(4 * kk + w.l4, a.q - 1) * a.n_pad + w.l16) * 8);
+  }
+  constexpr int BB = block_bytes(PREC);
+  const bool colok = c < a.P;
+  // this lane's dwords of the column block's chunk (see operand_block)
+  char* opc = PASS == 2 ? (char*)a.yop + (c >> 5) * (a.n_pad / kChunk) * (int64_t)BB + (c & 31) * 16 + 4 * w.l4 : nullptr;
+  f64x4 acc[NT];
+  uint32_t oa[NT];
+#pragma unroll
+  for (int x = 0; x < NT; ++x) {
+    acc[x] = f64x4{0.0, 0.0, 0.0, 0.0};
+    oa[x] = (uint32_t)((min(16 * x + w.l16, a.q - 1) * a.n_pad + w.l4) * 8);
+  }
+  double s1 = 0.0, s2 = 0.0, sl = 0.0, mx = 0.0;
+  for (int ch = w.ch_lo; ch < w.ch_hi; ++ch) {
+    const bool whole = (int64_t)(ch + 1) * kChunk <= a.n;
+    const char* qc = (const char*)(a.Q + (int64_t)ch * kChunk);
+    // the chunk's loads are issued together
+    f64x4 y[4];
+    double qv[4][KK];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      y[b] = prep_y<F64>(colp, (int64_t)ch * kChunk + 16 * b + w.l4, a.n, whole);
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) qv[b][kk] = gload<double>(qc + 128 * b + oq[kk]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int64_t s0 = (int64_t)ch * kChunk + 16 * b + w.l4;
+      f64x4 v = y[b];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = whole || s0 + 4 * i < a.n ? v[i] - pc.mean : 0.0;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+        v = __builtin_amdgcn_mfma_f64_16x16x4f64(qv[b][kk], nq[kk], v, 0, 0, 0);
+      if constexpr (PASS == 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s1 += v[i] * v[i];
+      } else if constexpr (PASS == 1) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const double vs = v[i] * inv16;
+          mx = fmax(mx, fabs(vs - (double)f16_to_float(f16_bits_rn((float)vs))));
+        }
+      } else {
+        f64x4 st;
+        char* p = opc + (int64_t)ch * BB + (b >> 1) * 512;
+        if constexpr (PREC == kFP32) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float f = (float)(v[i] * inv);
+            if (colok) gstore(p + (4 * (b & 1) + i) * 1024, f);
+            st[i] = (double)f;
+          }
+        } else {
+          uint32_t hb[4], lb[4];
+          if constexpr (PREC == kSplit8) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const double vs = v[i] * inv16;
+              hb[i] = f16_bits_rn((float)vs);
+              st[i] = (double)f16_to_float(hb[i]);
+              lb[i] = __float_as_uint(float_to_odd((vs - st[i]) * lo_up));
+            }
+            int lo = __builtin_amdgcn_cvt_pk_fp8_f32(__uint_as_float(lb[0]), __uint_as_float(lb[1]), 0, false);
+            lo = __builtin_amdgcn_cvt_pk_fp8_f32(__uint_as_float(lb[2]), __uint_as_float(lb[3]), lo, true);
+            const float lf[4] = {__builtin_amdgcn_cvt_f32_fp8(lo, 0), __builtin_amdgcn_cvt_f32_fp8(lo, 1),
+                                 __builtin_amdgcn_cvt_f32_fp8(lo, 2), __builtin_amdgcn_cvt_f32_fp8(lo, 3)};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const double lv = (double)lf[i] * lo_down;
+              sl += lv;
+              st[i] += lv;
+            }
+            if (colok) gstore(p + 4096 + (b & 1) * 1024, lo);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              split_parts(PREC, v[i] * inv, &hb[i], &lb[i]);
+              st[i] = PREC == kSplit16 ? (double)f16_to_float(hb[i]) + (double)f16_to_float(lb[i])
+                                       : (double)bf16_to_float(hb[i]) + (double)bf16_to_float(lb[i]);
+            }
+            if (colok) {
+              gstore(p + 4096 + 2 * (b & 1) * 1024, lb[0] | (lb[2] << 16));
+              gstore(p + 4096 + 2 * (b & 1) * 1024 + 1024, lb[1] | (lb[3] << 16));
+            }
+          }
+          if (colok) {
+            gstore(p + 2 * (b & 1) * 1024, hb[0] | (hb[2] << 16));
+            gstore(p + 2 * (b & 1) * 1024 + 1024, hb[1] | (hb[3] << 16));
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s1 += st[i];
+          s2 += st[i] * st[i];
+        }
+#pragma unroll
+        for (int x = 0; x < NT; ++x)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(gload<double>(qc + 128 * b + 32 * i + oa[x]), st[i], acc[x], 0, 0,
+                                                         0);
+      }
+    }
+  }
+  if constexpr (PASS == 0) {
+    s1 = prep_col_sum(s1);
+    if (w.l4 == 0) a.part[prep_at(a, 0, w.seg, c)] = s1;
+  } else if constexpr (PASS == 1) {
+    mx = fmax(mx, __shfl_xor(mx, 16));
+    mx = fmax(mx, __shfl_xor(mx, 32));
+    if (w.l4 == 0) a.part[prep_at(a, 0, w.seg, c)] = mx;
+  } else {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a.part[prep_at(a, 16 * t + 4 * i + w.l4, w.seg, c)] = acc[t][i];
+    s1 = prep_col_sum(s1);
+    s2 = prep_col_sum(s2);
+    sl = prep_col_sum(sl);
+    if (w.l4 == 0) {
+      a.part[prep_at(a, kPrepSlotV, w.seg, c)] = s1;
+      a.part[prep_at(a, kPrepSlotVV, w.seg, c)] = s2;
+      a.part[prep_at(a, kPrepSlotL, w.seg, c)] = sl;
+    }
+  }
+}
+
+// per-column constants from the sums of passes A and D (one wave per column)
+__global__ __launch_bounds__(256) void prep_finish_kernel(PrepArgs a, int prec) {
+  const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (p >= a.P) return;
+  const int64_t nc = 16 * (int64_t)a.n_tiles;
+  const char* colp = (const char*)a.Y + p * a.ldy * (a.y_fp64 ? 8 : 4);
+  double delta;
+  const PrepColumn pc = prep_column(a, p, a.y_fp64 ? *(const double*)colp : (double)*(const float*)colp, &delta);
+  const double sp = sqrt(pc.direct ? pc.r2 : a.r2[p]);
+  const bool valid = sp > 1e-12 * sqrt(pc.yc2);
+  const double* d = a.sums + kPrepSlots * nc + p;  // pass D's
+  if (lane == 0) {
+    double proj = 0.0;
+    for (int k = 0; k < a.q; ++k) proj += d[k * nc] * d[k * nc];
+    const double ny2 = d[kPrepSlotVV * nc] - proj;
+    a.scale[p] = (float)sp;
+    a.invny[p] = (valid && ny2 > 0.0) ? (float)(1.0 / sqrt(ny2)) : __builtin_nanf("");
+    if (prec == kSplit8) a.lscale[p] = (uint8_t)(127 - lo_shift(a.maxlo[p]));
+  }
+  if (lane < kSlots) {
+    float v = 0.0f;
+    if (lane == 0) v = (float)(-d[kPrepSlotV * nc]);
+    if (lane >= 1 && lane < a.q) v = (float)(-d[lane * nc]);
+    // FP16 + FP8 form with q <= 31: the last slot takes minus the column's sum of lo terms (see prep_kernel)
+    if (lane == kLoSlot && prec == kSplit8 && a.q <= kLoSlot) v = (float)(-d[kPrepSlotL * nc]);
+    a.cw[p * kSlots + lane] = v;
+  }
+}
 // test hook: raw operand columns (no centring / scaling)
 __global__ __launch_bounds__(kPrepThreads) void set_lscale_kernel(const float* __restrict__ V, int64_t ldv,
                                                                   int64_t n, uint8_t* lscale) {
@@ -773,7 +1180,6 @@ __global__ void tail_kernel(TailDev t, const PanelDev* __restrict__ panels, cons
 constexpr int kRedoWaves = 16;
 constexpr int kRedoThreads = 64 * kRedoWaves;
 static_assert(kRedoGroup == 16 && kRedoCols == 64 && kRedoThreads == kRedoGroup * kRedoCols, "redo shape");
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // a listed marker's genotype row: 2-bit codes (map: the calls of codes 0..3,
 // two bits each; miss: the missing code) or 8-bit dosages
@@ -2295,9 +2701,84 @@ hipError_t launch_cov_operands(const double* Q, int64_t n, int64_t n_pad, int q,
   return hipGetLastError();
 }
 
+// segments of the split preparation: about 8,192 waves in all, at least two chunks each
+static int prep_segments(int64_t n_pad, int64_t P) {
+  const int64_t tiles = (P + 15) / 16;
+  return (int)std::max<int64_t>(1, std::min<int64_t>((8192 + tiles - 1) / tiles, n_pad / kChunk / 2));
+}
+// cohorts from here on take the split preparation: below, its nine short
+// launches (about 40 us) cost more than prep_kernel's one (38 us at N = 2,000)
+constexpr int64_t kPrepSplitMin = 64 * kChunk;
+
+size_t prep_scratch_bytes(int64_t n_pad, int64_t P) {
+  if (n_pad < kPrepSplitMin) return 0;
+  const int64_t nc = (P + 15) / 16 * 16;
+  return sizeof(double) * (size_t)(nc * ((int64_t)kPrepSlots * (prep_segments(n_pad, P) + 2) + 2));
+}
+
+template <int PREC, int NT, bool F64>
+static void launch_prep_passes(const PrepArgs& a, unsigned grid, hipStream_t s) {
+  const dim3 b(256), g(grid);
+  const int64_t nc = 16 * (int64_t)a.n_tiles;
+  const double* part = a.part;
+  hipLaunchKernelGGL((prep_project_kernel<NT, F64>), g, b, 0, s, a);
+  hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, kPrepSlots), b, 0, s, part, a.sums, a.segs, nc);
+  hipLaunchKernelGGL((prep_residual_kernel<0, kFP32, NT, F64>), g, b, 0, s, a);
+  hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, 1), b, 0, s, part, a.r2, a.segs, nc);
+  if (PREC == kSplit8) {
+    hipLaunchKernelGGL((prep_residual_kernel<1, kSplit8, NT, F64>), g, b, 0, s, a);
+    hipLaunchKernelGGL(prep_sum_kernel<true>, dim3(a.n_tiles, 1), b, 0, s, part, a.maxlo, a.segs, nc);
+  }
+  hipLaunchKernelGGL((prep_residual_kernel<2, PREC, NT, F64>), g, b, 0, s, a);
+  hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, kPrepSlots), b, 0, s, part, a.sums + kPrepSlots * nc,
+                     a.segs, nc);
+  hipLaunchKernelGGL(prep_finish_kernel, dim3((unsigned)((a.P + 3) / 4)), b, 0, s, a, PREC);
+}
+
 hipError_t launch_prep(const void* Y, int y_fp64, int64_t ldy, int64_t n, int64_t n_pad, int64_t P,
                        const double* Q, int q, int prec, void* yop, float* scale, float* invny, float* cw,
-                       uint8_t* lscale, int32_t* flags, hipStream_t s) {
+                       uint8_t* lscale, int32_t* flags, void* scratch, hipStream_t s) {
+  if (scratch) {
+    PrepArgs a{};
+    a.Y = Y;
+    a.ldy = ldy;
+    a.n = n;
+    a.n_pad = n_pad;
+    a.P = P;
+    a.Q = Q;
+    a.q = q;
+    a.y_fp64 = y_fp64;
+    a.n_tiles = (int)((P + 15) / 16);
+    a.segs = prep_segments(n_pad, P);
+    a.yop = yop;
+    const int64_t nc = 16 * (int64_t)a.n_tiles;
+    a.sums = (double*)scratch;
+    a.r2 = a.sums + 2 * kPrepSlots * nc;
+    a.maxlo = a.r2 + nc;
+    a.part = a.maxlo + nc;
+    a.lscale = lscale;
+    a.scale = scale;
+    a.invny = invny;
+    a.cw = cw;
+    a.flags = flags;
+    const unsigned grid = (unsigned)(((int64_t)a.n_tiles * a.segs + 3) / 4);
+    auto go = [&](auto p) {
+      constexpr int PREC = decltype(p)::value;
+      if (q <= 16)
+        y_fp64 ? launch_prep_passes<PREC, 1, true>(a, grid, s) : launch_prep_passes<PREC, 1, false>(a, grid, s);
+      else
+        y_fp64 ? launch_prep_passes<PREC, 2, true>(a, grid, s) : launch_prep_passes<PREC, 2, false>(a, grid, s);
+    };
+    if (prec == kSplit8)
+      go(std::integral_constant<int, kSplit8>{});
+    else if (prec == kSplit16)
+      go(std::integral_constant<int, kSplit16>{});
+    else if (prec == kSplit)
+      go(std::integral_constant<int, kSplit>{});
+    else
+      go(std::integral_constant<int, kFP32>{});
+    return hipGetLastError();
+  }
   // q <= QS slots; two columns per workgroup (at P = 2,048 and q = 11 this
   // beats four, which leaves two waves per SIMD, and one), one for q > 24
   auto go = [&](auto kern, int cpw) {
@@ -2332,7 +2813,7 @@ hipError_t launch_set_operand(const float* V, int64_t ldv, int64_t n, int64_t n_
 }
 
 hipError_t launch_table(float4* table, double df, hipStream_t s) {
-  hipLaunchKernelGGL(table_kernel, dim3((kTabIntervals + 255) / 256), dim3(256), 0, s, table, df);
+  hipLaunchKernelGGL(table_kernel, dim3((kTabIntervals + kTabWave - 1) / kTabWave), dim3(64), 0, s, table, df);
   return hipGetLastError();
 }
 

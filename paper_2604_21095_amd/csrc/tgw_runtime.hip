@@ -423,9 +423,16 @@ extern "C" tgw_status tgw_prepare_phenotypes(const tgw_covariates* cov, int64_t 
   if (e == hipSuccess) e = hipMemsetAsync(p->invny, 0, p->P_pad * sizeof(float), s);
   if (e == hipSuccess) e = hipMemsetAsync(p->cw, 0, p->P_pad * kSlots * sizeof(float), s);
   if (e == hipSuccess) e = hipMemsetAsync(flags, 0, sizeof(int32_t), s);
+  // where there is no room for the scratch, the preparation that needs none runs
+  void* work = nullptr;
+  const size_t work_bytes = prep_scratch_bytes(cov->n_pad, n_pheno);
+  if (e == hipSuccess && work_bytes && dev_alloc(A, &work, work_bytes, s) != hipSuccess) {
+    work = nullptr;
+    (void)hipGetLastError();
+  }
   if (e == hipSuccess)
     e = launch_prep(d_Y, y_is_fp64, ldy, cov->n, cov->n_pad, n_pheno, cov->Q, cov->q, p->prec, p->yop, p->scale,
-                    p->invny, p->cw, p->lscale, flags, s);
+                    p->invny, p->cw, p->lscale, flags, work, s);
   if (e == hipSuccess) e = launch_table(p->table, (double)p->df, s);
   const PanelDev pd = panel_dev(p);
   if (e == hipSuccess) e = hipMemcpyAsync(p->d_dev, &pd, sizeof(pd), hipMemcpyHostToDevice, s);
@@ -434,6 +441,7 @@ extern "C" tgw_status tgw_prepare_phenotypes(const tgw_covariates* cov, int64_t 
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) (void)hipStreamSynchronize(s);  // nothing enqueued may still use flags
   dev_free(A, flags, s);
+  dev_free(A, work, s);
   if (e != hipSuccess) {
     tgw_panel_free(p);
     return hip_fail(e, "tgw_prepare_phenotypes");
