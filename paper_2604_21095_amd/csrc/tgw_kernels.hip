@@ -274,6 +274,250 @@ __global__ void cov_operand_kernel(const double* __restrict__ Q, int64_t n, int6
 }
 
 // ---------------------------------------------------------------------------
+// covariate QR by Cholesky, twice (Yamamoto, Nakatsukasa, Yanagisawa & Fukaya,
+// "Roundoff error analysis of the CholeskyQR2 algorithm", ETNA 44, 2015): the
+// Gram matrix of X = [1 | C] with unit columns gives R and Q1 = X R^-1, whose
+// own Gram matrix, the unit matrix to cond(X)^2 rounding errors, corrects it
+// to Q orthonormal to rounding.  Five launches instead of six per column.
+// Taken when every pivot of the first factorization is above kGramPivot
+// (condition below about 1e4: Q is then as accurate as the Householder QR's);
+// otherwise flags[2] is set, the caller runs the Householder QR above, and
+// that one also decides on rank deficiency.
+// The Householder QR's column signs are kept: R_jj = -sign(pivot) |R_jj|, the
+// pivots being those of Householder reflections on Q itself, which need only
+// its first q rows (for orthonormal columns a_j the reflection's products are
+// v^T v = 2 (1 + |a_jj|) and v^T a_k = -s a_jk).
+// The Gram matrices and products run on the FP64 matrix cores, W waves over
+// the sample chunks; the waves' 16 x 16 tiles are added in order.  The last
+// kernel also writes the Q^T g operands.
+// N = 23,000, K = 10: 0.39 ms in 67 launches -> 0.10 ms; bound by the latency
+// of five dependent launches.
+// ---------------------------------------------------------------------------
+constexpr double kGramPivot = 1e-8;  // squares: 1e-4 of a column's norm
+constexpr int kGramTiles = 3;        // (0,0), (0,1), (1,1) of 16 slots each
+struct GramArgs {
+  const double* C;
+  int64_t ldc, n, n_pad;
+  int q, waves;
+  double* part;   // [waves][kGramTiles][256]
+  double* coef;   // first and second q x q factors (kSlots x kSlots each), then R's diagonal
+  double* Q1;
+  double* Q;
+  int32_t* flags;
+  float* wop_fp32;
+  char* wop_hl[2];  // BF16 split, FP16 split
+};
+__device__ __forceinline__ double gram_x(const GramArgs& a, int k, int64_t i) {
+  if (k == 0 || k >= a.q) return k == 0 && i < a.n ? 1.0 : 0.0;
+  const double v = a.C[(int64_t)(k - 1) * a.ldc + (i < a.n ? i : 0)];
+  return i < a.n ? v : 0.0;
+}
+// the tiles a wave's Gram products leave: element (row 4 i + l4, column l16)
+template <int NT>
+__device__ __forceinline__ void gram_store(const GramArgs& a, int w, int l16, int l4, const f64x4 (&g)[kGramTiles]) {
+#pragma unroll
+  for (int t = 0; t < (NT == 1 ? 1 : kGramTiles); ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a.part[((int64_t)w * kGramTiles + t) * 256 + (4 * i + l4) * 16 + l16] = g[t][i];
+}
+
+// PASS 0: Gram of X; 1: Q1 = X M1 and its Gram; 2: Q = Q1 M2 and the operands
+template <int PASS, int NT>
+__global__ __launch_bounds__(64) void gram_kernel(GramArgs a) {
+  const int lane = threadIdx.x, l16 = lane & 15, l4 = lane >> 4;
+  const int w = blockIdx.x;
+  const int nch = (int)(a.n_pad / kChunk);
+  const int ch_lo = (int)((int64_t)nch * w / gridDim.x), ch_hi = (int)((int64_t)nch * (w + 1) / gridDim.x);
+  if (PASS == 2 && a.flags[2]) return;
+  constexpr int KK = 4 * NT;
+  double m[NT][KK];  // this pass's factor: element (4 kk + l4, 16 t + l16)
+  if constexpr (PASS > 0) {
+    const double* c = a.coef + (PASS - 1) * kSlots * kSlots;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) m[t][kk] = c[(4 * kk + l4) * kSlots + 16 * t + l16];
+  }
+  f64x4 g[kGramTiles];
+#pragma unroll
+  for (int t = 0; t < kGramTiles; ++t) g[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+  int bad = 0;
+  for (int ch = ch_lo; ch < ch_hi; ++ch) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int64_t s0 = (int64_t)ch * kChunk + 16 * b;
+      f64x4 d[NT];
+      if constexpr (PASS == 0) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            d[t][i] = gram_x(a, 16 * t + l16, s0 + 4 * i + l4);
+            if (!isfinite(d[t][i])) bad = 1;
+          }
+      } else {
+        double x[KK];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          const int k = 4 * kk + l4;
+          x[kk] = PASS == 1 ? gram_x(a, k, s0 + l16) : k < a.q ? a.Q1[(int64_t)k * a.n_pad + s0 + l16] : 0.0;
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          d[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) d[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[kk], m[t][kk], d[t], 0, 0, 0);
+          const int k = 16 * t + l16;
+          double* out = PASS == 1 ? a.Q1 : a.Q;
+          if (k < a.q) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[(int64_t)k * a.n_pad + s0 + 4 * i + l4] = d[t][i];
+          }
+          if constexpr (PASS == 2) {
+            // operand columns: slot k >= 1 <- Q[:, k]; slot 0 and slots >= q are zero
+            double v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = k >= 1 && k < a.q ? d[t][i] : 0.0;
+            // packed block t: hi part in column l16, lo part in column l16 + 16
+            // (of its first half; the second half is never read), dword l4 of
+            // step j = 2 (b & 1) + (i & 1) holding samples i and i + 2
+            if (t < hl_blocks(a.q)) {
+              const int64_t at = ((int64_t)t * nch + ch) * kBlockBytes + 2 * (b & 1) * 1024 + (b >> 1) * 512 + l16 * 16 + 4 * l4;
+#pragma unroll
+              for (int f = 0; f < 2; ++f) {
+                uint32_t hb[4], lb[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) split_parts(f == 0 ? kSplit : kSplit16, v[i], &hb[i], &lb[i]);
+                char* p = a.wop_hl[f] + at;
+                gstore(p, hb[0] | (hb[2] << 16));
+                gstore(p + 1024, hb[1] | (hb[3] << 16));
+                gstore(p + 256, lb[0] | (lb[2] << 16));
+                gstore(p + 1024 + 256, lb[1] | (lb[3] << 16));
+              }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              a.wop_fp32[(int64_t)ch * 2048 + (4 * (b & 1) + i) * 256 + (32 * (b >> 1) + k) * 4 + l4] = (float)v[i];
+          }
+        }
+        if constexpr (PASS == 2 && NT == 1) {  // the FP32 block's other 16 columns
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            a.wop_fp32[(int64_t)ch * 2048 + (4 * (b & 1) + i) * 256 + (32 * (b >> 1) + 16 + l16) * 4 + l4] = 0.0f;
+        }
+      }
+      if constexpr (PASS < 2) {  // a product's accumulator layout is both operands' layout
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          g[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[0][i], d[0][i], g[0], 0, 0, 0);
+          if constexpr (NT == 2) {
+            g[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[0][i], d[1][i], g[1], 0, 0, 0);
+            g[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[1][i], d[1][i], g[2], 0, 0, 0);
+          }
+        }
+      }
+    }
+  }
+  if constexpr (PASS < 2) gram_store<NT>(a, w, l16, l4, g);
+  if (bad) a.flags[0] = 1;
+}
+
+// One workgroup: the Gram matrix from the waves' tiles, its Cholesky factor R
+// and the next pass's factor R^-1 (SECOND: with the column signs; also the
+// rank check of the Householder QR on R's diagonal).
+template <bool SECOND>
+__global__ __launch_bounds__(1024) void gram_factor_kernel(GramArgs a) {
+  __shared__ double sum[4][256];
+  __shared__ double G[kSlots][kSlots + 1], R[kSlots][kSlots + 1], inv[kSlots][kSlots + 1], T[kSlots][kSlots + 1];
+  __shared__ double dsc[kSlots], sgn[kSlots];
+  __shared__ int ill;
+  const int tid = threadIdx.x, q = a.q;
+  if (SECOND && a.flags[2]) return;  // uniform
+  if (tid == 0) ill = 0;
+  for (int t = 0; t < (q <= 16 ? 1 : kGramTiles); ++t) {
+    const int r = tid >> 8, e = tid & 255;
+    double v = 0.0;
+#pragma unroll 8
+    for (int w = a.waves * r / 4; w < a.waves * (r + 1) / 4; ++w) v += a.part[((int64_t)w * kGramTiles + t) * 256 + e];
+    sum[r][e] = v;
+    __syncthreads();
+    if (r == 0) {
+      v = ((sum[0][e] + sum[1][e]) + sum[2][e]) + sum[3][e];
+      const int row = (e >> 4) + (t == 2 ? 16 : 0), col = (e & 15) + (t >= 1 ? 16 : 0);
+      G[row][col] = v;
+      if (t == 1) G[col][row] = v;
+    }
+    __syncthreads();
+  }
+  const int i = tid >> 5, k = tid & 31;  // one thread per element
+  if (tid < kSlots) {
+    const double d = tid < q ? G[tid][tid] : 1.0;
+    if (!SECOND && !(d > 0.0 && isfinite(d))) ill = 1;
+    dsc[tid] = SECOND || !(d > 0.0) ? 1.0 : 1.0 / sqrt(d);
+  }
+  __syncthreads();
+  const bool in = i < q && k < q;
+  double gv = in ? G[i][k] * dsc[i] * dsc[k] : 0.0;
+  for (int j = 0; j < q; ++j) {  // right-looking: thread (i, k) keeps its element
+    if (i == j) G[j][k] = gv;
+    __syncthreads();
+    const double piv = G[j][j];
+    if (tid == 0 && !(piv > (SECOND ? 0.5 : kGramPivot))) ill = 1;
+    const double rj = sqrt(piv > 0.0 ? piv : 1.0);
+    if (i == j) R[j][k] = k >= j && k < q ? gv / rj : 0.0;
+    if (i > j && k > j && in) gv -= G[j][i] / rj * (G[j][k] / rj);
+    __syncthreads();
+  }
+  if (ill) {
+    if (tid == 0) a.flags[2] = 1;
+    return;
+  }
+  if (tid < kSlots) {  // column tid of R^-1, from its diagonal up
+    for (int r = kSlots - 1; r >= 0; --r) {
+      double v = 0.0;
+      if (tid < q && r <= tid) {
+        v = r == tid ? 1.0 : 0.0;
+        for (int x = r + 1; x <= tid; ++x) v -= R[r][x] * inv[x][tid];
+        v /= R[r][r];
+      }
+      inv[r][tid] = v;
+    }
+  }
+  __syncthreads();
+  double* coef = a.coef + (SECOND ? kSlots * kSlots : 0);
+  double* rdiag = a.coef + 2 * kSlots * kSlots;
+  if (!SECOND) {
+    coef[i * kSlots + k] = dsc[i] * inv[i][k];
+    if (tid < q) rdiag[tid] = R[tid][tid] / dsc[tid];
+    return;
+  }
+  // first q rows of Q = Q1 R^-1, then the signs
+  double t = 0.0;
+  if (in)
+    for (int x = 0; x <= k; ++x) t += a.Q1[(int64_t)x * a.n_pad + i] * inv[x][k];
+  T[i][k] = t;
+  __syncthreads();
+  for (int j = 0; j < q; ++j) {
+    const double p = T[j][j];
+    const double s = p > 0.0 ? -1.0 : 1.0;
+    if (tid == 0) sgn[j] = s;
+    const double u = in && i > j && k > j ? T[i][j] * s * T[j][k] / (1.0 + fabs(p)) : 0.0;
+    __syncthreads();
+    if (in && i > j && k > j) T[i][k] += u;
+    __syncthreads();
+  }
+  coef[i * kSlots + k] = k < q ? inv[i][k] * sgn[k] : 0.0;
+  if (tid == 0) {  // every |R_jj| above 1e-10 max |R_ii|
+    double mx = 0.0;
+    for (int j = 0; j < q; ++j) mx = fmax(mx, fabs(rdiag[j] * R[j][j]));
+    int rd = 0;
+    for (int j = 0; j < q; ++j)
+      if (!(fabs(rdiag[j] * R[j][j]) > 1e-10 * mx)) rd = 1;
+    a.flags[1] = rd;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // phenotype preparation (Eq. 1 + standardization): one workgroup per CPW
 // columns, so that each element of Q read from L2 serves CPW columns; QS >= q
 // slots of the projections are kept per column.  Every column's arithmetic
@@ -2690,6 +2934,48 @@ hipError_t launch_qr(const double* C, int64_t ldc, int64_t n, int64_t n_pad, int
     hipLaunchKernelGGL(qr_reflect_kernel, g, b, 0, s, xj, Q, n, n_pad, q, j, (int64_t)j, (const double*)fv);
   }
   hipLaunchKernelGGL(qr_rank_kernel, dim3(1), dim3(64), 0, s, (const double*)rdiag, q, flags);
+  return hipGetLastError();
+}
+
+static int gram_waves(int64_t n_pad) {  // about four chunks a wave, at most 256 waves
+  return (int)std::max<int64_t>(1, std::min<int64_t>(256, n_pad / kChunk / 4));
+}
+size_t gram_scratch_doubles(int64_t n_pad) {
+  return (size_t)gram_waves(n_pad) * kGramTiles * 256 + 2 * kSlots * kSlots + kSlots;
+}
+
+hipError_t launch_gram_qr(const double* C, int64_t ldc, int64_t n, int64_t n_pad, int q, double* Q1, double* Q,
+                          double* scratch, int32_t* flags, void* wop_fp32, void* const* wop_hl, hipStream_t s) {
+  if (q < 1 || q > kSlots) return hipErrorInvalidValue;
+  GramArgs a{};
+  a.C = C;
+  a.ldc = ldc;
+  a.n = n;
+  a.n_pad = n_pad;
+  a.q = q;
+  a.waves = gram_waves(n_pad);
+  a.coef = scratch;
+  a.part = scratch + 2 * kSlots * kSlots + kSlots;
+  a.Q1 = Q1;
+  a.Q = Q;
+  a.flags = flags;
+  a.wop_fp32 = (float*)wop_fp32;
+  a.wop_hl[0] = (char*)wop_hl[kSplit];
+  a.wop_hl[1] = (char*)wop_hl[kSplit16];
+  const dim3 g(a.waves), b(64), last((unsigned)(n_pad / kChunk));
+  if (q <= 16) {
+    hipLaunchKernelGGL((gram_kernel<0, 1>), g, b, 0, s, a);
+    hipLaunchKernelGGL(gram_factor_kernel<false>, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL((gram_kernel<1, 1>), g, b, 0, s, a);
+    hipLaunchKernelGGL(gram_factor_kernel<true>, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL((gram_kernel<2, 1>), last, b, 0, s, a);
+  } else {
+    hipLaunchKernelGGL((gram_kernel<0, 2>), g, b, 0, s, a);
+    hipLaunchKernelGGL(gram_factor_kernel<false>, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL((gram_kernel<1, 2>), g, b, 0, s, a);
+    hipLaunchKernelGGL(gram_factor_kernel<true>, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL((gram_kernel<2, 2>), last, b, 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -322,18 +322,27 @@ extern "C" tgw_status tgw_fit_covariates(int64_t n_samples, int32_t n_cov, const
   hipError_t e = dmalloc(A, &cov->Q, (size_t)cov->q * cov->n_pad, s);
   if (e == hipSuccess) e = dmalloc(A, &X, (size_t)cov->q * cov->n_pad, s);
   if (e == hipSuccess) e = dmalloc(A, &rdiag, (size_t)cov->q, s);
-  if (e == hipSuccess) e = dmalloc(A, &qrs, (size_t)kQrScratch, s);
-  if (e == hipSuccess) e = dmalloc(A, &flags, 2, s);
+  if (e == hipSuccess) e = dmalloc(A, &qrs, std::max((size_t)kQrScratch, gram_scratch_doubles(cov->n_pad)), s);
+  if (e == hipSuccess) e = dmalloc(A, &flags, 3, s);
   if (e == hipSuccess) e = dev_alloc(A, &cov->wop_fp32, (size_t)cov->n_chunks * kBlockBytes, s);
   for (int k : {(int)kSplit, (int)kSplit16})
     if (e == hipSuccess) e = dev_alloc(A, &cov->wop_hl[k], (size_t)hl_blocks(cov->q) * cov->n_chunks * kBlockBytes, s);
-  if (e == hipSuccess) e = hipMemsetAsync(flags, 0, 2 * sizeof(int32_t), s);
-  if (e == hipSuccess) e = launch_qr(d_C, ldc, n_samples, cov->n_pad, cov->q, X, cov->Q, rdiag, qrs, flags, s);
+  int32_t hf[3] = {0, 0, 0};
+  auto read_flags = [&] {
+    if (e == hipSuccess) e = hipMemcpyAsync(hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+  };
+  if (e == hipSuccess) e = hipMemsetAsync(flags, 0, sizeof(hf), s);
   if (e == hipSuccess)
-    e = launch_cov_operands(cov->Q, n_samples, cov->n_pad, cov->q, cov->wop_fp32, cov->wop_hl, s);
-  int32_t hf[2] = {0, 0};
-  if (e == hipSuccess) e = hipMemcpyAsync(hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+    e = launch_gram_qr(d_C, ldc, n_samples, cov->n_pad, cov->q, X, cov->Q, qrs, flags, cov->wop_fp32, cov->wop_hl, s);
+  read_flags();
+  if (e == hipSuccess && !hf[0] && hf[2]) {  // ill-conditioned: the Householder QR, which also decides on the rank
+    e = hipMemsetAsync(flags, 0, sizeof(hf), s);
+    if (e == hipSuccess) e = launch_qr(d_C, ldc, n_samples, cov->n_pad, cov->q, X, cov->Q, rdiag, qrs, flags, s);
+    if (e == hipSuccess)
+      e = launch_cov_operands(cov->Q, n_samples, cov->n_pad, cov->q, cov->wop_fp32, cov->wop_hl, s);
+    read_flags();
+  }
   if (e != hipSuccess) (void)hipStreamSynchronize(s);  // nothing enqueued may still use the temporaries
   cleanup();
   if (e != hipSuccess) {
