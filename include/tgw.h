@@ -350,7 +350,9 @@ tgw_status tgw_plan_autotune(tgw_plan* plan, const uint8_t* d_geno, int64_t n_ma
  * ranges gives bitwise the same outputs as one call when every boundary is a
  * multiple of 512 markers from m_begin (any boundary for FP32 and the 16-bit
  * split forms; the FP16 hi + FP8 lo form orders its FP32 accumulation by a
- * marker's row in the 512-marker tile).
+ * marker's row in the 512-marker tile).  Above 65,536 samples the FP16 forms
+ * add up to eight segments of the samples in order, each accumulated in FP32
+ * from zero; the segments follow from the sample count alone.
  * Asynchronous: enqueues kernels on `stream`, allocates nothing and does not
  * synchronize; capturable in a HIP graph.  The plan's workspace is reused, so
  * calls with the same plan must not run concurrently on different streams.
@@ -399,7 +401,7 @@ tgw_status tgw_plan_profile_read(tgw_plan* plan, void* stream, double* main_ms, 
  * tgw_scan over the given panels without a plan.  Everything a plan holds
  * (column-block tables, per-panel constants, output table, per-block
  * workspace, the FP64 list of collinear markers, the tail list) lives in a
- * static device array of 64 MiB that every GPU the library runs on holds
+ * static device array of 128 MiB that every GPU the library runs on holds
  * until the process ends; the call allocates nothing and does not
  * synchronize.  Same arguments and results as tgw_scan (the panels' order is
  * the outputs' order), with these differences:

@@ -21,6 +21,28 @@ constexpr int kSlots = 32;      // correction slots per (marker, panel): dmu, Q^
 // the last slot, free when q <= 31, carries the FP8 lo pass's change of centring
 // (FP16 + FP8 form): (c - c8) per marker against -(sum of lo terms) per column
 constexpr int kLoSlot = kSlots - 1;
+// Cohorts of more than kSegMin chunks (65,536 samples): the FP16 forms' FP32
+// accumulators are the sums of up to kSegMax segments of the chunks (of at
+// least kSegMin, the last one of the rest), each accumulated from zero, added
+// in order, whichever kernel computes them.  So segments can run side by side
+// where there are few tiles, and the rounding error grows with the segment
+// instead of the cohort.  One segment up to there: the order of the
+// accumulation is then that of a single run over the chunks.  At N = 500,001
+// the outputs of the FP16 forms are 1.0e-5 to 2.1e-5 (2-norm of -log10 p) from
+// those of a single run, whose own error is that large; BF16 hi + lo, where the
+// single run is 1.5e-5 to 3.5e-5 off, keeps it, so that its results stay what
+// they were to 2e-5, and so does FP32.
+constexpr int kSegMin = 1024;
+constexpr int kSegMax = 8;
+// chunks of a segment (prec 2 and 3: the FP16 forms): a multiple of the eight that the small tiles load together
+__host__ __device__ constexpr int seg_chunks(int prec, int n_chunks) {
+  const int even = (n_chunks + kSegMax * 8 - 1) / (kSegMax * 8) * 8;
+  return prec < 2 || n_chunks <= kSegMin ? n_chunks : even < kSegMin ? kSegMin : even;
+}
+__host__ __device__ constexpr int n_segments(int prec, int n_chunks) {
+  const int len = seg_chunks(prec, n_chunks);
+  return len < 1 ? 1 : (n_chunks + len - 1) / len;
+}
 constexpr int kMaxCov = 31;     // K <= 31 so that q = K + 1 <= 32 slots
 constexpr int kMaxPanelsPerBind = 32;
 // Covariate-collinear markers.  The contraction's FP32 rounding error scales
@@ -187,6 +209,15 @@ struct GemmArgs {
   float wscale;      // undoes the operand scale of the Q columns
   int32_t lo_slot;   // the last slot carries c - c8
   RedoDev redo;
+  // segments of the sample chunks (n_segments); their sums between kernels
+  // (small tiles) or over a workgroup's run (wide tiles: a tile's accumulators
+  // per workgroup)
+  int32_t n_segs;
+  int32_t seg_len;   // chunks of a segment (seg_chunks)
+  float* part;
+  int64_t part_bytes;
+  int64_t row0;      // small tiles: row of the first marker tile
+  int32_t ct0;       // and the first column tile
   int32_t lo_tile;   // small tiles, FP16 + FP8 form: the wide tile whose order of the FP8 lo step they follow
 };
 
@@ -283,6 +314,16 @@ TileShape tile_shape_for(int idx, int prec, bool g8 = false);  // the shape a pr
 // largest resident grid for a tile shape (occupancy x CUs), rounded to 8 XCDs
 int gemm_grid(int idx, int prec, int mode, int n_cu, bool g8 = false);
 int tile_alias(int idx, int prec, bool g8 = false);  // smallest tile index that runs the same kernel
+// the wide tiles over segments (n_segs > 1): the shapes, and a grid of at most
+// n_cu workgroups whose accumulators fit in a.part
+TileShape seg_tile_shape(int idx, int prec, bool g8);
+hipError_t launch_gemm_seg(int idx, int prec, const GemmArgs& a, int n_cu, hipStream_t s, bool g8);
+// bytes of the segments' buffer: what a scan wants, and the least it runs with
+int64_t seg_part_bytes(int n_segs, int n_cu);
+constexpr int64_t kSegTileBytes = 512 * 128 * 4;  // a wide tile's accumulators
+// eight workgroups of wide tiles (one per XCD); the kSegMax segments of one
+// small tile (64 KiB each at most) fit too
+constexpr int64_t kSegPartLeast = 8 * kSegTileBytes;
 hipError_t launch_gemm(int idx, int prec, int mode, const GemmArgs& a, int grid, hipStream_t s, bool g8 = false);
 // precisions that 8-bit dosages run in (exact re-centred operand: FP32 and the FP16 split)
 __host__ __device__ constexpr bool g8_supported(int prec) { return prec == kFP32 || prec == kSplit16 || prec == kSplit8; }
@@ -290,11 +331,11 @@ __host__ __device__ constexpr bool g8_supported(int prec) { return prec == kFP32
 // beside the tests
 TileShape small_shape(int idx);
 // the small tile of a marker block, or -1 where the plan's tile is the faster one
-int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_cu);
+int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_segs, int n_cu);
 // of a one-panel block whose Q^T g (nqb packed blocks) the same kernel forms, or -1
-int small_fused_shape(int prec, bool g8, int64_t nm, int n_cb, int nqb, int n_cu);
+int small_fused_shape(int prec, bool g8, int64_t nm, int n_cb, int nqb, int n_segs, int n_cu);
 // of the Q^T g contraction alone
-int small_q_shape(int prec, int64_t nm, int n_cb, int n_cu);
+int small_q_shape(int prec, int64_t nm, int n_cb, int n_segs, int n_cu);
 const void* gemm_small_fp32_fn(int idx, int mode, bool g8);
 hipError_t launch_gemm_small(int idx, int prec, int mode, int nqb, const GemmArgs& a, hipStream_t s, bool g8);
 

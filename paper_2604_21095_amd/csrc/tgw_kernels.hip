@@ -1,14 +1,19 @@
 // gfx950 kernels of the phenotype-panel linear association scan.
 //
-//  qr_*_kernel        FP64 Householder QR of [1 | C] -> Q (Methods 2.2: Q
-//                     spans the covariate space and has orthonormal columns)
-//  prep_kernel        Eq. 1 + column standardization, once per panel, FP64;
-//                     writes the contraction operand (FP32 or BF16 hi + lo)
+//  gram_*_kernel      FP64 orthonormal basis Q of [1 | C] by Cholesky twice
+//                     (Methods 2.2: Q spans the covariate space and has
+//                     orthonormal columns)
+//  qr_*_kernel        the same by Householder QR, for ill-conditioned covariates
+//  prep_*_kernel      Eq. 1 + column standardization, once per panel, FP64;
+//                     writes the contraction operand (FP32 or hi + lo);
+//                     prep_kernel alone for cohorts of under 4,096 samples
 //  table_kernel       -log10 p nodes for |t| in [0, 40] at the panel's df
 //  stats_kernel       exact integer per-marker counts -> mean, ||g_c||^2,
 //                     re-centring constant and the 2-bit decode table
-//  gemm_kernel        the contraction of Eq. 2 on the matrix cores with the
-//                     fused epilogue (r, t of Eq. 3, beta, SE, -log10 p)
+//  gemm_wide_kernel,  the contraction of Eq. 2 on the matrix cores with the
+//  gemm_kernel        fused epilogue (r, t of Eq. 3, beta, SE, -log10 p);
+//                     small tiles and Q^T g are in tgw_small.hip
+//  redo_kernel        FP64 path of covariate-collinear markers
 //  finalize_kernel    ||g_res||^2 = ||g_c||^2 - sum_k (q_k^T g)^2
 //  tail_kernel        FP64 -log10 p for |t| > 40
 #include "tgw_device.h"
@@ -1419,7 +1424,7 @@ __global__ void tail_kernel(TailDev t, const PanelDev* __restrict__ panels, cons
 // depends on neither the list nor the grid.  A lane reads two or three dwords
 // of the panel operand per four values.  600 listed markers x 300 phenotypes
 // at N = 23,000, K = 13: 15.7 ms with one column per thread and scalar
-// operand reads, 0.40 ms here.
+// operand reads, 0.64 ms here.
 // ---------------------------------------------------------------------------
 constexpr int kRedoWaves = 16;
 constexpr int kRedoThreads = 64 * kRedoWaves;
@@ -1755,7 +1760,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(GemmArgs a) {
 
     u32x4 breg[WN][RPB];
     // this lane's genotype bytes of the chunk: 8 (2-bit codes) or 32 (dosages).
-    // The 32-column shape (the Q^T g contraction) does little work per
+    // The 32-column shapes do little work per
     // chunk, so it keeps a ring of AD chunks of its rows in flight to cover
     // the memory latency (the chunk loop is unrolled by AD so that the ring
     // is indexed statically); the others keep one chunk ahead.
@@ -2097,7 +2102,12 @@ constexpr int waitcnt_vm_only(int vm) { return waitcnt_vm_lgkm0(vm) | (0xF << 8)
 // G8: 8-bit dosage rows (FP16 split only): each stage holds the tile's 64
 // bytes per marker; a lane reads the two dwords of its row that each K16 step
 // needs and builds FP16 q - c as the register-staged kernel does.
-template <int PREC, int MODE, int NW, int WMF, int WN = 4, bool G8 = false>
+// SEG: the accumulators are added up over segments (see kSegMin), one after the
+// other, in this workgroup's part of a.part.  Each segment of a tile is a pass
+// of its own through the tile loop, and moves 512 KiB against the 14 MiB that
+// its chunks read (16,384 markers x 2,048 phenotypes, N = 70,001, whole scan:
+// 5.66 ms with and without).
+template <int PREC, int MODE, int NW, int WMF, int WN = 4, bool G8 = false, bool SEG = false>
 __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
   static_assert(PREC != kFP32, "the wide kernel runs the split forms");
   static_assert(!G8 || PREC == kSplit16 || PREC == kSplit8, "8-bit dosages run the FP16 split forms here");
@@ -2153,7 +2163,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
   const int64_t wlo = W * xcd / 8;
   const int64_t whi = W * (xcd + 1) / 8;
 
-  for (int64_t w = wlo + slot; w < whi; w += nslots) {
+  int seg = 0;  // SEG: a tile's segments in turn
+  for (int64_t w = wlo + slot; w < whi;) {
     int mtile, ctile;
     grouped_tile(w, a.n_mtiles, a.n_ctiles, mtile, ctile);
     const char* bop[WN];
@@ -2205,11 +2216,12 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[fm][fn][i] = 0.0f;
 
-    const int nch = a.n_chunks;
-    // chunk ch (clamped to the last one: the surplus copies land in stages
-    // nobody reads again) into stage st
+    int nch = a.n_chunks, ch_lo = 0;  // chunks of the segment, its first chunk
+    // chunk ch of the segment (clamped to the last one: the surplus copies land
+    // in stages nobody reads again) into stage st
     auto dma = [&](int ch, int st) {
       ch = ch < nch ? ch : nch - 1;
+      if constexpr (SEG) ch += ch_lo;
       char* stage = smem + st * STAGE_BYTES;
 #pragma unroll
       for (int q = 0; q < B_OPS; ++q) {
@@ -2376,6 +2388,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
         }
     };
 
+    if constexpr (SEG) {
+      ch_lo = seg * a.seg_len;
+      nch = ch_lo + a.seg_len < a.n_chunks ? a.seg_len : a.n_chunks - ch_lo;
+    }
     // prologue: chunks 0..NSTAGE-1 requested, chunk 0 awaited
 #pragma unroll
     for (int c = 0; c < NSTAGE; ++c) dma(c, c);
@@ -2638,6 +2654,47 @@ __global__ __launch_bounds__(NW * 64) void gemm_wide_kernel(GemmArgs a) {
     }
     __builtin_amdgcn_s_waitcnt(0);  // surplus copies have landed
     __syncthreads();                // all waves are done with the stages
+    if constexpr (SEG) {
+      // the sums so far, 16 bytes per lane and access, in this workgroup's part.
+      // Every segment but the last ends here, so the accumulators don't live
+      // on (kept over the segments they spill: 7.3 against 5.8 ms, 16,384
+      // markers x 2,048 phenotypes, N = 70,001)
+      char* ws = (char*)a.part + (int64_t)blockIdx.x * kSegTileBytes + tid * 16;
+      const bool last = seg + 1 == a.n_segs;
+      if (seg > 0) {
+#pragma unroll
+        for (int f = 0; f < WMF * WN; ++f) {
+          // a few fragments' loads in flight at a time, as registers allow
+          if (f % (NW == 4 ? 4 : 2) == 0) asm volatile("" : "+v"(ws)::"memory");
+          f32x16& v = acc[f / WN][f % WN];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const u32x4 e = gload<u32x4>(ws + (f * 4 + i) * NT * 16);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[4 * i + t] = __uint_as_float(e[t]) + v[4 * i + t];
+          }
+        }
+      }
+      if (!last) {
+#pragma unroll
+        for (int f = 0; f < WMF * WN; ++f) {
+          asm volatile("" : "+v"(ws)::"memory");
+          const f32x16& v = acc[f / WN][f % WN];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            u32x4 e;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) e[t] = __float_as_uint(v[4 * i + t]);
+            gstore(ws + (f * 4 + i) * NT * 16, e);
+          }
+        }
+        __builtin_amdgcn_s_waitcnt(0);  // the next segment's waits count its copies alone
+        ++seg;
+        continue;
+      }
+      seg = 0;
+    }
+    w += nslots;
 
     if constexpr (MODE == kRaw) {
 #pragma unroll
@@ -2901,6 +2958,34 @@ int gemm_grid(int idx, int prec, int mode, int n_cu, bool g8) {
   int g = occ * n_cu;
   g = (g / 8) * 8;
   return g < 8 ? 8 : g;
+}
+
+// the wide tiles over segments: tiles 1 and (FP16 + FP8, 2-bit codes) 6, else
+// tile 0.  The register-staged shapes have no segments: with 8-bit dosages,
+// 8,192 markers x 1,024 phenotypes, N = 131,072, they take 9.7 (FP16 + FP8) and
+// 10.6 ms (FP16 split) where segments on small and wide tiles take 4.5 and 5.8
+static int seg_tile(int idx, int prec, bool g8) { return idx == 1 || (idx == 6 && prec == kSplit8 && !g8) ? idx : 0; }
+TileShape seg_tile_shape(int idx, int prec, bool g8) { return kShapes[seg_tile(idx, prec, g8)]; }
+template <int PREC, bool G8>
+static const void* seg_fn(int tile) {
+  if constexpr (PREC == kSplit8 && !G8)
+    if (tile == 6) return (const void*)gemm_wide_kernel<PREC, kTest, 4, 2, 8, G8, true>;
+  return tile == 1 ? (const void*)gemm_wide_kernel<PREC, kTest, 8, 2, 4, G8, true>
+                   : (const void*)gemm_wide_kernel<PREC, kTest, 4, 4, 4, G8, true>;
+}
+int64_t seg_part_bytes(int n_segs, int n_cu) {
+  return n_segs <= 1 ? 0 : std::max<int64_t>(n_cu * kSegTileBytes, kSegPartLeast);
+}
+hipError_t launch_gemm_seg(int idx, int prec, const GemmArgs& a, int n_cu, hipStream_t s, bool g8) {
+  const int tile = seg_tile(idx, prec, g8);
+  const void* fn = nullptr;
+  if (prec == kSplit8) fn = g8 ? seg_fn<kSplit8, true>(tile) : seg_fn<kSplit8, false>(tile);
+  if (prec == kSplit16) fn = g8 ? seg_fn<kSplit16, true>(tile) : seg_fn<kSplit16, false>(tile);
+  const int64_t grid = std::min<int64_t>(n_cu, a.part_bytes / kSegTileBytes) / 8 * 8;
+  if (!fn || grid < 8) return hipErrorInvalidValue;
+  GemmArgs arg = a;
+  void* params[] = {&arg};
+  return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kShapes[tile].waves * 64), params, 0, s);
 }
 
 hipError_t launch_gemm(int idx, int prec, int mode, const GemmArgs& a, int grid, hipStream_t s, bool g8) {

@@ -227,6 +227,9 @@ struct tgw_plan {
   // FP16 + FP8 form with q <= 31 in every panel: the FP8 lo pass centres on
   // the integer rint(c), its shift removed through the last correction slot
   bool lo_int = false;
+  int n_segs = 1;            // segments of the sample chunks, and their buffer (also of Q^T g)
+  float* part = nullptr;
+  int64_t part_bytes = 0;
   std::vector<int> grid_main8;
   bool profile = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_events;
@@ -515,6 +518,7 @@ extern "C" void tgw_plan_free(tgw_plan* pl) {
   dev_free(A, pl->redo_count, nullptr);
   dev_free(A, pl->tail_entries, nullptr);
   dev_free(A, pl->tail_count, nullptr);
+  dev_free(A, pl->part, nullptr);
   delete pl;
 }
 
@@ -667,6 +671,15 @@ extern "C" tgw_status tgw_plan_create(const tgw_panel* const* panels, int32_t n_
   if (e == hipSuccess) e = dmalloc(pl->mem, &pl->redo_count, (size_t)n_panels);
   if (e == hipSuccess) e = dmalloc(pl->mem, &pl->tail_entries, (size_t)pl->tail_cap);
   if (e == hipSuccess) e = dmalloc(pl->mem, &pl->tail_count, 1);
+  pl->n_segs = n_segments(pl->prec, pl->n_chunks);
+  if (e == hipSuccess && pl->n_segs > 1) {  // with less room than a scan wants it takes more and smaller steps
+    for (int64_t want = seg_part_bytes(pl->n_segs, pl->n_cu);; want = std::max(kSegPartLeast, want / 2)) {
+      e = dev_alloc(pl->mem, (void**)&pl->part, (size_t)want, nullptr);
+      pl->part_bytes = want;
+      if (e == hipSuccess || want == kSegPartLeast) break;
+      (void)hipGetLastError();
+    }
+  }
   if (e == hipSuccess) e = hipMemcpy(pl->d_cb_main, cbm.data(), cbm.size() * sizeof(ColBlock), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(pl->d_cb_w, cbw.data(), cbw.size() * sizeof(ColBlock), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(pl->d_panels, pdv.data(), pdv.size() * sizeof(PanelDev), hipMemcpyHostToDevice);
@@ -762,6 +775,10 @@ static GemmArgs base_args(const tgw_plan* pl, const ScanCall& c, int64_t m0, int
   a.hits = pl->hits;
   a.m_begin = c.m_begin;
   a.gunit = c.code == TGW_CODE_DOSAGE8 ? kDosage8Unit : 1.0f;
+  a.n_segs = pl->n_segs;
+  a.seg_len = seg_chunks(pl->prec, pl->n_chunks);
+  a.part = pl->part;
+  a.part_bytes = pl->part_bytes;
   return a;
 }
 
@@ -775,9 +792,9 @@ static MainPath main_path(const tgw_plan* pl, int code, int64_t nm) {
   const bool g8 = code == TGW_CODE_DOSAGE8;
   MainPath p;
   const int nqb = pl->n_panels == 1 && pl->w_mode == kRawHL ? hl_blocks(pl->panels[0]->cov->q) : 0;
-  p.small = small_fused_shape(pl->prec, g8, nm, pl->n_cb, nqb, pl->n_cu);
+  p.small = small_fused_shape(pl->prec, g8, nm, pl->n_cb, nqb, pl->n_segs, pl->n_cu);
   p.fused = p.small >= 0;
-  if (!p.fused) p.small = small_test_shape(pl->prec, g8, nm, pl->n_cb, pl->n_cu);
+  if (!p.fused) p.small = small_test_shape(pl->prec, g8, nm, pl->n_cb, pl->n_segs, pl->n_cu);
   return p;
 }
 
@@ -802,7 +819,7 @@ static hipError_t enqueue_block_stats(tgw_plan* pl, const ScanCall& c, int64_t m
   if (mp.fused) return hipSuccess;  // the main kernel forms Q^T g and ||g_res|| itself
   GemmArgs a = base_args(pl, c, m0, nm);
   const bool g8 = c.code == TGW_CODE_DOSAGE8;
-  const int shape = small_q_shape(pl->prec, nm, pl->n_cb_w, pl->n_cu);
+  const int shape = small_q_shape(pl->prec, nm, pl->n_cb_w, pl->n_segs, pl->n_cu);
   const TileShape ws = small_shape(shape);
   a.cblocks = pl->d_cb_w;
   a.n_cblocks = pl->n_cb_w;
@@ -846,7 +863,9 @@ static hipError_t enqueue_main(tgw_plan* pl, const ScanCall& c, int64_t m0, int6
   GemmArgs a = base_args(pl, c, m0, nm);
   const bool g8 = c.code == TGW_CODE_DOSAGE8;
   const bool small = mp.small >= 0;
-  const TileShape ts = small ? small_shape(mp.small) : tile_shape_for(tile, pl->prec, g8);
+  const TileShape ts = small            ? small_shape(mp.small)
+                       : pl->n_segs > 1 ? seg_tile_shape(tile, pl->prec, g8)
+                                        : tile_shape_for(tile, pl->prec, g8);
   a.cblocks = pl->d_cb_main;
   a.n_cblocks = pl->n_cb;
   a.n_ctiles = (pl->n_cb + ts.wn_frags - 1) / ts.wn_frags;
@@ -861,6 +880,7 @@ static hipError_t enqueue_main(tgw_plan* pl, const ScanCall& c, int64_t m0, int6
   auto launch = [&] {
     if (small)
       return launch_gemm_small(mp.small, pl->prec, kTest, mp.fused ? hl_blocks(pl->panels[0]->cov->q) : 0, a, s, g8);
+    if (pl->n_segs > 1) return launch_gemm_seg(tile, pl->prec, a, pl->n_cu, s, g8);
     return launch_gemm(tile, pl->prec, kTest, a, g8 ? pl->grid_main8[tile] : pl->grid_main[tile], s, g8);
   };
   if (!pl->profile) return launch();
@@ -1144,7 +1164,8 @@ constexpr size_t kStaticBytes = size_t(64) << 20;
 constexpr int kStaticPanels = kMaxPanelsPerBind;  // 32
 constexpr int kStaticColBlocks = 32768;           // 2^20 phenotype columns in all
 constexpr int kStaticTail = 1 << 16;
-static __device__ __align__(256) unsigned char scratch[kStaticBytes];
+constexpr size_t kStaticSegBytes = size_t(64) << 20;  // segments of cohorts of more than 65,536 samples
+static __device__ __align__(256) unsigned char scratch[kStaticBytes + kStaticSegBytes];
 
 static hipError_t static_scratch_address(char** p) {
   void* a = nullptr;
@@ -1326,6 +1347,9 @@ extern "C" tgw_status tgw_scan_static(const tgw_panel* const* panels, int32_t n_
   pl.invh = invh;
   pl.redo_entries = redo_entries;
   pl.redo_count = redo_count;
+  pl.n_segs = n_segments(prec, p0->cov->n_chunks);
+  pl.part = (float*)(base + kStaticBytes);
+  pl.part_bytes = kStaticSegBytes;
   pl.max_chunks = max_chunks;
   pl.tail_entries = tail;
   pl.tail_count = tail_count;

@@ -3,6 +3,8 @@
 // Q^T g contraction of the split forms.
 #include "tgw_device.h"
 
+#include <algorithm>
+
 namespace tgw {
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
@@ -30,8 +32,15 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 // The decode (56 VALU instructions per fragment and chunk in the FP16 + FP8
 // form, about the issue time of the matrix-core steps against one column
 // block) runs a step ahead of the matrix-core instructions it feeds.
+//
+// PHASE (cohorts of more than kSegMin chunks, whose accumulators are the sums
+// of segments, added in order): 1 leaves the accumulators of one segment of a
+// tile in a.part, 2 adds a tile's segments and finishes it, 0 does all of a
+// shorter cohort at once.  A cohort of 500,001 samples has 8 segments: with
+// 4,096 markers and 8 phenotypes, 256 workgroups instead of 32 (scan 3.92 ->
+// 0.65 ms; r's error against FP64 1.5e-5 -> 1.6e-6 of its size).
 // ---------------------------------------------------------------------------
-template <int PREC, int MODE, int WMF, int WN, int NQB, bool G8>
+template <int PREC, int MODE, int WMF, int WN, int NQB, bool G8, int PHASE>
 __global__ __launch_bounds__(256, 2) void gemm_small_kernel(GemmArgs a) {
   constexpr int NW = 4, NT = NW * 64, TM = NW * WMF * 32;
   constexpr bool HL = MODE == kRawHL;
@@ -58,22 +67,29 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(GemmArgs a) {
   constexpr int IH_BYTES = MODE == kTest ? TM * 8 : 0;
   constexpr int TAB_BYTES = MODE == kTest ? kTabIntervals * 16 : 0;
   constexpr int WS_BYTES = FUSED ? TM * WSP * 4 : 0;
-  constexpr int EPI_BYTES = STAGE_BYTES + IH_BYTES + TAB_BYTES + WS_BYTES;
-  __shared__ __attribute__((aligned(16))) char smem[2 * STG > EPI_BYTES ? 2 * STG : EPI_BYTES];
+  constexpr int EPI_BYTES = PHASE == 1 ? 0 : STAGE_BYTES + IH_BYTES + TAB_BYTES + WS_BYTES;
+  constexpr int LOOP_BYTES = PHASE == 2 ? 16 : 2 * STG;
+  __shared__ __attribute__((aligned(16))) char smem[LOOP_BYTES > EPI_BYTES ? LOOP_BYTES : EPI_BYTES];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5;
   const int r32 = lane & 31;
-  const int64_t W = (int64_t)a.n_mtiles * a.n_ctiles;
+  const int64_t tiles = (int64_t)a.n_mtiles * a.n_ctiles;
+  const int64_t W = PHASE == 1 ? tiles * a.n_segs : tiles;  // segment by segment
   const int xcd = blockIdx.x & 7;
   const int64_t wlo = W * xcd / 8, whi = W * (xcd + 1) / 8;
   const int64_t w = wlo + (blockIdx.x >> 3);
   if (w >= whi) return;
+  const int seg = PHASE == 1 ? (int)(w / tiles) : 0;
+  const int64_t tile_w = w - seg * tiles;
   int mtile, ctile;
-  grouped_tile(w, a.n_mtiles, a.n_ctiles, mtile, ctile);
-  const int nch = a.n_chunks;
+  grouped_tile(tile_w, a.n_mtiles, a.n_ctiles, mtile, ctile);
+  ctile += a.ct0;
+  // the chunks [ch_lo, nch) of this workgroup
+  const int ch_lo = PHASE == 1 ? seg * a.seg_len : 0;
+  const int nch = PHASE == 1 && ch_lo + a.seg_len < a.n_chunks ? ch_lo + a.seg_len : a.n_chunks;
 
   // this wave's 1 KiB pieces of a stage: source, chunk stride and chunk of each
   const char* bsrc[NQ];
@@ -89,7 +105,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(GemmArgs a) {
     } else {
       const int qp = piece - WN * PPF;
       const int qb = qp / (NQB ? QPF : 1);
-      const char* wop = HL ? a.cblocks[ctile].op : (const char*)a.panels[0].wop + (int64_t)qb * nch * kBlockBytes;
+      const char* wop = HL ? a.cblocks[ctile].op : (const char*)a.panels[0].wop + (int64_t)qb * a.n_chunks * kBlockBytes;
       bsrc[q] = wop + (qp % QPC) * 1024;
       bch[q] = (qp % QPF) / QPC;
       bstr[q] = kBlockBytes;
@@ -114,7 +130,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(GemmArgs a) {
     for (int q = 0; q < NQ; ++q) *(u32x4*)(smem + buf * STG + (q * NW + wave) * 1024 + lane16) = breg[q];
   };
 
-  const int64_t rowbase = (int64_t)mtile * TM + wave * (WMF * 32);
+  const int64_t rowbase = a.row0 + (int64_t)mtile * TM + wave * (WMF * 32);
   const uint8_t* ap[WMF];
   uint2 lut[WMF];
   uint32_t lut8[WMF];
@@ -264,106 +280,141 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(GemmArgs a) {
       bq[set][fq] = *(const u32x4*)(stage + QOFF + (fq * CS + c) * QB + j * 1024 + lane16);
   };
 
-  load_stage(0);
-  load_rows(0, raw[0]);
-  if constexpr (G8) load_rows(2, raw[1]);
-  store_stage(0, 0);
-  load_stage(CS);
-  __syncthreads();
-  if constexpr (!G8) {
-    swap_rows(raw[0]);
-    expand(0, 0);
-    if constexpr (F8) {
-      expand8(0, 0);
-      expand8(0, 1);
+  // this wave's accumulators of a segment, [fragment and block][element][lane]
+  constexpr int NACC = WMF * (WN + NQB);
+  auto part_at = [&](int sg) {
+    return a.part + (((int64_t)sg * tiles + tile_w) * NW + wave) * (NACC * 16 * 64) + lane;
+  };
+  auto each_acc = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fm = 0; fm < WMF; ++fm) {
+#pragma unroll
+      for (int fn = 0; fn < WN; ++fn) f(acc[fm][fn], fm * (WN + NQB) + fn);
+#pragma unroll
+      for (int fq = 0; fq < NQB; ++fq) f(accq[fm][fq], fm * (WN + NQB) + WN + fq);
     }
-  }
-  operand(0, 0, A[0]);
-  read_b(smem, 0, 0, 0);
-  for (int ch0 = 0; ch0 < nch; ch0 += GCH) {
-    if constexpr (!G8) load_rows(ch0 + GCH, raw[1]);
+  };
+  if constexpr (PHASE == 2) {
+    for (int sg = 0; sg < a.n_segs; ++sg) {
+      const float* p = part_at(sg);
+      each_acc([&](f32x16& v, int x) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < GCH; ++u) {
-      const int buf = (u / CS) & 1;
-      const char* stage = smem + buf * STG;
-      if (!G8 && u == 7) swap_rows(raw[1]);
-      i32x8 B8[F8 ? WN : 1];
+        for (int i = 0; i < 16; ++i) {
+          const float e = gload<float>(p + (x * 16 + i) * 64);
+          v[i] = sg == 0 ? e : v[i] + e;
+        }
+      });
+    }
+  } else {
+    load_stage(ch_lo);
+    load_rows(ch_lo, raw[0]);
+    if constexpr (G8) load_rows(ch_lo + 2, raw[1]);
+    store_stage(0, ch_lo);
+    load_stage(ch_lo + CS);
+    __syncthreads();
+    if constexpr (!G8) {
+      swap_rows(raw[0]);
+      expand(0, 0);
       if constexpr (F8) {
-#pragma unroll
-        for (int fn = 0; fn < WN; ++fn) {
-          const char* tile = stage + (fn * CS + u % CS) * SB + 4096;
-          const u32x4 p0 = *(const u32x4*)(tile + lane16);
-          const u32x4 p1 = *(const u32x4*)(tile + 1024 + lane16);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            B8[fn][t] = (int)p0[t];
-            B8[fn][4 + t] = (int)p1[t];
-          }
-        }
-        if constexpr (!G8) {
-#pragma unroll
-          for (int fm = 0; fm < WMF; ++fm) A8[fm] = A8n[fm];
-        }
+        expand8(0, 0);
+        expand8(0, 1);
       }
+    }
+    operand(0, 0, A[0]);
+    read_b(smem, 0, 0, 0);
+    for (int ch0 = ch_lo; ch0 < nch; ch0 += GCH) {
+      if constexpr (!G8) load_rows(ch0 + GCH, raw[1]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int cs = j & 1, ns = cs ^ 1;
-        if (j < 3) read_b(stage, u % CS, j + 1, ns);
-        if (j == 3) {
-          if (u % CS == CS - 1) {  // this chunk's stage is read: the next one's turn
-            store_stage(buf ^ 1, ch0 + u + 1);
-            load_stage(ch0 + u + 1 + CS);
-            __syncthreads();
-            read_b(smem + (buf ^ 1) * STG, 0, 0, ns);
-          } else {
-            read_b(stage, u % CS + 1, 0, ns);
-          }
-        }
-        // decode for the next step (and the next chunk's FP8 operand)
-        if constexpr (!G8) {
-          if (j == 1) expand(u, 1);
-          if (j == 3) expand(u + 1, 0);
-          if constexpr (F8) {
-            if (j == 0) expand8(u + 1, 0);
-            if (j == 2) expand8(u + 1, 1);
-          }
-          operand(j < 3 ? u : u + 1, (j + 1) & 3, A[ns]);
-        } else {
-          operand(j < 3 ? u : u + 1, (j + 1) & 3, A[ns]);
-          if (j == 2 && (u & 1)) load_rows(ch0 + u + 3, raw[(u >> 1) & 1]);  // this pair's codes are decoded
-        }
-#pragma unroll
-        for (int fm = 0; fm < WMF; ++fm) {
-#pragma unroll
-          for (int fq = 0; fq < NQB; ++fq) accq[fm][fq] = mfma16<PREC>(A[cs][fm], bq[cs][fq], accq[fm][fq]);
-#pragma unroll
-          for (int fn = 0; fn < WN; ++fn) acc[fm][fn] = mfma16<PREC>(A[cs][fm], bh[cs][fn], acc[fm][fn]);
-        }
-        if constexpr (LO16) {
-#pragma unroll
-          for (int fm = 0; fm < WMF; ++fm)
-#pragma unroll
-            for (int fn = 0; fn < WN; ++fn) acc[fm][fn] = mfma16<PREC>(A[cs][fm], bl[cs][fn], acc[fm][fn]);
-        }
+      for (int u = 0; u < GCH; ++u) {
+        const int buf = (u / CS) & 1;
+        const char* stage = smem + buf * STG;
+        if (!G8 && u == 7) swap_rows(raw[1]);
+        i32x8 B8[F8 ? WN : 1];
         if constexpr (F8) {
 #pragma unroll
-          for (int fm = 0; fm < WMF; ++fm)
+          for (int fn = 0; fn < WN; ++fn) {
+            const char* tile = stage + (fn * CS + u % CS) * SB + 4096;
+            const u32x4 p0 = *(const u32x4*)(tile + lane16);
+            const u32x4 p1 = *(const u32x4*)(tile + 1024 + lane16);
 #pragma unroll
-            for (int fn = 0; fn < WN; ++fn)
-              if (G8 ? j == 2 : los[fm][fn] == j)
-                acc[fm][fn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A8[fm], B8[fn], acc[fm][fn], 0, 0, 0,
-                                                                              127, 0, bscale[fn]);
+            for (int t = 0; t < 4; ++t) {
+              B8[fn][t] = (int)p0[t];
+              B8[fn][4 + t] = (int)p1[t];
+            }
+          }
+          if constexpr (!G8) {
+#pragma unroll
+            for (int fm = 0; fm < WMF; ++fm) A8[fm] = A8n[fm];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int cs = j & 1, ns = cs ^ 1;
+          if (j < 3) read_b(stage, u % CS, j + 1, ns);
+          if (j == 3) {
+            if (u % CS == CS - 1) {  // this chunk's stage is read: the next one's turn
+              store_stage(buf ^ 1, ch0 + u + 1);
+              load_stage(ch0 + u + 1 + CS);
+              __syncthreads();
+              read_b(smem + (buf ^ 1) * STG, 0, 0, ns);
+            } else {
+              read_b(stage, u % CS + 1, 0, ns);
+            }
+          }
+          // decode for the next step (and the next chunk's FP8 operand)
+          if constexpr (!G8) {
+            if (j == 1) expand(u, 1);
+            if (j == 3) expand(u + 1, 0);
+            if constexpr (F8) {
+              if (j == 0) expand8(u + 1, 0);
+              if (j == 2) expand8(u + 1, 1);
+            }
+            operand(j < 3 ? u : u + 1, (j + 1) & 3, A[ns]);
+          } else {
+            operand(j < 3 ? u : u + 1, (j + 1) & 3, A[ns]);
+            if (j == 2 && (u & 1)) load_rows(ch0 + u + 3, raw[(u >> 1) & 1]);  // this pair's codes are decoded
+          }
+#pragma unroll
+          for (int fm = 0; fm < WMF; ++fm) {
+#pragma unroll
+            for (int fq = 0; fq < NQB; ++fq) accq[fm][fq] = mfma16<PREC>(A[cs][fm], bq[cs][fq], accq[fm][fq]);
+#pragma unroll
+            for (int fn = 0; fn < WN; ++fn) acc[fm][fn] = mfma16<PREC>(A[cs][fm], bh[cs][fn], acc[fm][fn]);
+          }
+          if constexpr (LO16) {
+#pragma unroll
+            for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+              for (int fn = 0; fn < WN; ++fn) acc[fm][fn] = mfma16<PREC>(A[cs][fm], bl[cs][fn], acc[fm][fn]);
+          }
+          if constexpr (F8) {
+#pragma unroll
+            for (int fm = 0; fm < WMF; ++fm)
+#pragma unroll
+              for (int fn = 0; fn < WN; ++fn)
+                if (G8 ? j == 2 : los[fm][fn] == j)
+                  acc[fm][fn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A8[fm], B8[fn], acc[fm][fn], 0, 0, 0,
+                                                                                127, 0, bscale[fn]);
+          }
         }
       }
-    }
-    if constexpr (!G8) {
+      if constexpr (!G8) {
 #pragma unroll
-      for (int fm = 0; fm < WMF; ++fm)
+        for (int fm = 0; fm < WMF; ++fm)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) raw[0][fm][i] = raw[1][fm][i];
+          for (int i = 0; i < 4; ++i) raw[0][fm][i] = raw[1][fm][i];
+      }
     }
+    __syncthreads();  // all waves are done with the stages
   }
-  __syncthreads();  // all waves are done with the stages
+  if constexpr (PHASE == 1) {
+    float* p = part_at(seg);
+    each_acc([&](f32x16& v, int x) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) gstore(p + (x * 16 + i) * 64, v[i]);
+    });
+    return;
+  }
 
   if constexpr (HL) {
     // slot col0 + r32, r32 < 16: hi product (column r32) plus lo product
@@ -519,18 +570,18 @@ const TileCost& tile_cost(int prec, bool g8) {
   static const TileCost fp32 = {41900, {4803, 8678, 8113, 14292, 12862}, {3734, 7097, 6223, 11933, 10726}};
   return prec == kSplit8 ? (g8 ? f8_g8 : f8) : prec == kSplit16 ? (g8 ? f16_g8 : f16) : prec == kSplit ? bf16 : fp32;
 }
-int64_t rounds(int64_t nm, int n_cb, const TileShape& t, int n_cu) {
+int64_t rounds(int64_t nm, int n_cb, const TileShape& t, int n_cu, int n_segs = 1) {
   const int64_t tiles = ((nm + t.tm() - 1) / t.tm()) * ((n_cb + t.wn_frags - 1) / t.wn_frags);
-  return (tiles + n_cu - 1) / n_cu;
+  return (tiles * n_segs + n_cu - 1) / n_cu;
 }
 }  // namespace
 
-int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_cu) {
+int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_segs, int n_cu) {
   const TileCost& c = tile_cost(prec, g8);
-  int64_t best = rounds(nm, n_cb, TileShape{4, 4, 4}, n_cu) * c.wide;
+  int64_t best = rounds(nm, n_cb, TileShape{4, 4, 4}, n_cu) * c.wide * n_segs;
   int pick = -1;
   for (int i = 0; i < kNumSmall; ++i) {
-    const int64_t r = rounds(nm, n_cb, kSmall[i], n_cu);
+    const int64_t r = rounds(nm, n_cb, kSmall[i], n_cu, n_segs);
     const int64_t t = r <= 1 ? c.alone[i] : r * c.shared[i];
     if (t < best) best = t, pick = i;
   }
@@ -542,69 +593,102 @@ int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_cu) {
 // to fit in one tile.  One column block and one covariate block: two
 // fragments per wave halve the operand reads (1,450 cycles per tile against
 // 2 x 830), but 256-row tiles leave more of the last round empty.
-int small_fused_shape(int prec, bool g8, int64_t nm, int n_cb, int nqb, int n_cu) {
+int small_fused_shape(int prec, bool g8, int64_t nm, int n_cb, int nqb, int n_segs, int n_cu) {
   if (prec == kFP32 || nqb < 1 || n_cb > 2) return -1;
   if (n_cb == 2) return 2;
   if (nqb > 1 || g8) return 0;
-  const int64_t r0 = rounds(nm, n_cb, kSmall[0], n_cu), r1 = rounds(nm, n_cb, kSmall[1], n_cu);
+  const int64_t r0 = rounds(nm, n_cb, kSmall[0], n_cu, n_segs), r1 = rounds(nm, n_cb, kSmall[1], n_cu, n_segs);
   return r1 * (r1 > 1 ? 1450 : 1720) < r0 * (r0 > 1 ? 830 : 1000) ? 1 : 0;
 }
 
 // 256-row tiles once they fill the GPU (100,000 markers, N = 23,000: 0.21 ms
 // against 0.25 ms on 128-row ones), else 128-row ones (4,096 markers, N =
-// 500,001: 2.0 against 3.2 ms)
-int small_q_shape(int prec, int64_t nm, int n_cb, int n_cu) {
-  return prec != kFP32 && rounds(nm, n_cb, kSmall[1], n_cu) > 1 ? 1 : 0;
+// 500,001 in one segment: 2.0 against 3.2 ms)
+int small_q_shape(int prec, int64_t nm, int n_cb, int n_segs, int n_cu) {
+  return prec != kFP32 && rounds(nm, n_cb, kSmall[1], n_cu, n_segs) > 1 ? 1 : 0;
 }
 
-template <int PREC, int NQB, bool G8>
+template <int PREC, int NQB, bool G8, int PH>
 static const void* small_fn(int idx) {
   switch (idx) {
-    case 0: return (const void*)gemm_small_kernel<PREC, kTest, 1, 1, NQB, G8>;
+    case 0: return (const void*)gemm_small_kernel<PREC, kTest, 1, 1, NQB, G8, PH>;
     case 1:
-      if constexpr (NQB < 2 && !(G8 && NQB)) return (const void*)gemm_small_kernel<PREC, kTest, 2, 1, NQB, G8>;
+      if constexpr (NQB < 2 && !(G8 && NQB)) return (const void*)gemm_small_kernel<PREC, kTest, 2, 1, NQB, G8, PH>;
       return nullptr;
-    case 2: return (const void*)gemm_small_kernel<PREC, kTest, 1, 2, NQB, G8>;
+    case 2: return (const void*)gemm_small_kernel<PREC, kTest, 1, 2, NQB, G8, PH>;
     case 3:
-      if constexpr (NQB == 0) return (const void*)gemm_small_kernel<PREC, kTest, 2, 2, NQB, G8>;
+      if constexpr (NQB == 0) return (const void*)gemm_small_kernel<PREC, kTest, 2, 2, NQB, G8, PH>;
       return nullptr;
     case 4:
-      if constexpr (NQB == 0) return (const void*)gemm_small_kernel<PREC, kTest, 1, 4, NQB, G8>;
+      if constexpr (NQB == 0) return (const void*)gemm_small_kernel<PREC, kTest, 1, 4, NQB, G8, PH>;
       return nullptr;
   }
   return nullptr;
 }
 
-template <int PREC, bool G8>
+template <int PREC, bool G8, int PH>
 static const void* small_fn_q(int idx, int nqb) {
-  return nqb == 0 ? small_fn<PREC, 0, G8>(idx) : nqb == 1 ? small_fn<PREC, 1, G8>(idx) : small_fn<PREC, 2, G8>(idx);
+  return nqb == 0   ? small_fn<PREC, 0, G8, PH>(idx)
+         : nqb == 1 ? small_fn<PREC, 1, G8, PH>(idx)
+                    : small_fn<PREC, 2, G8, PH>(idx);
 }
 
-template <int PREC, bool G8>
+template <int PREC, bool G8, int PH>
 static const void* small_hl_fn(int idx) {
-  return idx == 0   ? (const void*)gemm_small_kernel<PREC, kRawHL, 1, 0, 1, G8>
-         : idx == 1 ? (const void*)gemm_small_kernel<PREC, kRawHL, 2, 0, 1, G8>
+  return idx == 0   ? (const void*)gemm_small_kernel<PREC, kRawHL, 1, 0, 1, G8, PH>
+         : idx == 1 ? (const void*)gemm_small_kernel<PREC, kRawHL, 2, 0, 1, G8, PH>
                     : nullptr;
 }
 
-hipError_t launch_gemm_small(int idx, int prec, int mode, int nqb, const GemmArgs& a, hipStream_t s, bool g8) {
-  const void* fn = nullptr;
-  if (prec == kFP32) {
-    fn = gemm_small_fp32_fn(idx, mode, g8);
-  } else if (mode == kRawHL) {
-    if (prec == kSplit16) fn = g8 ? small_hl_fn<kSplit16, true>(idx) : small_hl_fn<kSplit16, false>(idx);
-    if (prec == kSplit && !g8) fn = small_hl_fn<kSplit, false>(idx);
+template <int PH>
+static const void* small_kernel(int idx, int prec, int mode, int nqb, bool g8) {
+  if (mode == kRawHL) {
+    if (prec == kSplit16) return g8 ? small_hl_fn<kSplit16, true, PH>(idx) : small_hl_fn<kSplit16, false, PH>(idx);
+    if constexpr (PH == 0)
+      if (prec == kSplit && !g8) return small_hl_fn<kSplit, false, PH>(idx);
   } else if (mode == kTest) {
-    if (prec == kSplit8) fn = g8 ? small_fn_q<kSplit8, true>(idx, nqb) : small_fn_q<kSplit8, false>(idx, nqb);
-    if (prec == kSplit16) fn = g8 ? small_fn_q<kSplit16, true>(idx, nqb) : small_fn_q<kSplit16, false>(idx, nqb);
-    if (prec == kSplit && !g8) fn = small_fn_q<kSplit, false>(idx, nqb);
+    if (prec == kSplit8) return g8 ? small_fn_q<kSplit8, true, PH>(idx, nqb) : small_fn_q<kSplit8, false, PH>(idx, nqb);
+    if (prec == kSplit16)
+      return g8 ? small_fn_q<kSplit16, true, PH>(idx, nqb) : small_fn_q<kSplit16, false, PH>(idx, nqb);
+    if constexpr (PH == 0)
+      if (prec == kSplit && !g8) return small_fn_q<kSplit, false, PH>(idx, nqb);
   }
+  return nullptr;
+}
+
+static hipError_t launch_tiles(const void* fn, const GemmArgs& a, int64_t tiles, hipStream_t s) {
   if (!fn) return hipErrorInvalidValue;
-  const int64_t tiles = (int64_t)a.n_mtiles * a.n_ctiles;
   const int64_t grid = (tiles + 7) / 8 * 8;  // ceil(tiles / 8) workgroups per XCD's range
   GemmArgs arg = a;
   void* params[] = {&arg};
   return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(256), params, 0, s);
+}
+
+hipError_t launch_gemm_small(int idx, int prec, int mode, int nqb, const GemmArgs& a, hipStream_t s, bool g8) {
+  const int64_t tiles = (int64_t)a.n_mtiles * a.n_ctiles;
+  if (prec == kFP32) return launch_tiles(gemm_small_fp32_fn(idx, mode, g8), a, tiles, s);
+  if (a.n_segs <= 1) return launch_tiles(small_kernel<0>(idx, prec, mode, nqb, g8), a, tiles, s);
+  // as many tiles at a time as a.part holds the segments of: whole rows of
+  // column tiles where one row fits, else parts of a row
+  const TileShape t = kSmall[idx];
+  const int64_t fit = a.part_bytes / ((int64_t)t.waves * t.wm_frags * (mode == kRawHL ? 1 : t.wn_frags + nqb) * 4096 *
+                                      a.n_segs);
+  if (fit < 1) return hipErrorInvalidValue;
+  const int nc = (int)std::min<int64_t>(a.n_ctiles, fit);
+  const int64_t nm = fit / nc;
+  hipError_t e = hipSuccess;
+  for (int64_t m0 = 0; e == hipSuccess && m0 < a.n_mtiles; m0 += nm)
+    for (int c0 = 0; e == hipSuccess && c0 < a.n_ctiles; c0 += nc) {
+      GemmArgs b = a;
+      b.row0 = m0 * t.tm();
+      b.ct0 = c0;
+      b.n_mtiles = (int)std::min<int64_t>(nm, a.n_mtiles - m0);
+      b.n_ctiles = std::min(nc, a.n_ctiles - c0);
+      const int64_t n = (int64_t)b.n_mtiles * b.n_ctiles;
+      e = launch_tiles(small_kernel<1>(idx, prec, mode, nqb, g8), b, n * a.n_segs, s);
+      if (e == hipSuccess) e = launch_tiles(small_kernel<2>(idx, prec, mode, nqb, g8), b, n, s);
+    }
+  return e;
 }
 
 }  // namespace tgw
