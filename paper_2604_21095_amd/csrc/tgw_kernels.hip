@@ -822,11 +822,11 @@ __global__ __launch_bounds__(256, 4) void prep_project_kernel(PrepArgs a) {
   const char* col = (const char*)a.Y + w.col * a.ldy * (F64 ? 8 : 4);
   const double y0 = F64 ? *(const double*)col : (double)*(const float*)col;
   f64x4 acc[NT];
-  uint32_t oq[NT];
+  int64_t oq[NT];
 #pragma unroll
   for (int x = 0; x < NT; ++x) {
     acc[x] = f64x4{0.0, 0.0, 0.0, 0.0};
-    oq[x] = (uint32_t)((min(16 * x + w.l16, a.q - 1) * a.n_pad + w.l4) * 8);
+    oq[x] = (min(16 * x + w.l16, a.q - 1) * a.n_pad + w.l4) * 8;
   }
   double sv = 0.0, svv = 0.0;
   int bad = 0;
@@ -957,22 +957,22 @@ __global__ __launch_bounds__(256, PASS == 2 ? 3 : 4) void prep_residual_kernel(P
   const double lo_up = ldexp(1.0, lsh), lo_down = ldexp(1.0, -lsh);
   constexpr int KK = 4 * NT;
   double nq[KK];
-  uint32_t oq[KK];
+  int64_t oq[KK];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
     nq[kk] = -prep_qty(a, 4 * kk + w.l4, c, delta);
-    oq[kk] = (uint32_t)((min(4 * kk + w.l4, a.q - 1) * a.n_pad + w.l16) * 8);
+    oq[kk] = (min(4 * kk + w.l4, a.q - 1) * a.n_pad + w.l16) * 8;
   }
   constexpr int BB = block_bytes(PREC);
   const bool colok = c < a.P;
   // this lane's dwords of the column block's chunk (see operand_block)
   char* opc = PASS == 2 ? (char*)a.yop + (c >> 5) * (a.n_pad / kChunk) * (int64_t)BB + (c & 31) * 16 + 4 * w.l4 : nullptr;
   f64x4 acc[NT];
-  uint32_t oa[NT];
+  int64_t oa[NT];
 #pragma unroll
   for (int x = 0; x < NT; ++x) {
     acc[x] = f64x4{0.0, 0.0, 0.0, 0.0};
-    oa[x] = (uint32_t)((min(16 * x + w.l16, a.q - 1) * a.n_pad + w.l4) * 8);
+    oa[x] = (min(16 * x + w.l16, a.q - 1) * a.n_pad + w.l4) * 8;
   }
   double s1 = 0.0, s2 = 0.0, sl = 0.0, mx = 0.0;
   for (int ch = w.ch_lo; ch < w.ch_hi; ++ch) {
@@ -1550,8 +1550,8 @@ __global__ __launch_bounds__(kRedoThreads) void redo_kernel(RedoArgs a) {
     {
       f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
       // step i contracts samples 16 b + 4 l4 + i: a lane reads 32 bytes of its slot's column at once
-      const uint32_t o0 = (uint32_t)((min(l16, q - 1) * a.n_pad + 4 * l4) * 8);
-      const uint32_t o1 = (uint32_t)((min(l16 + 16, q - 1) * a.n_pad + 4 * l4) * 8);
+      const int64_t o0 = (min(l16, q - 1) * a.n_pad + 4 * l4) * 8;
+      const int64_t o1 = (min(l16 + 16, q - 1) * a.n_pad + 4 * l4) * 8;
       for (int ch = ch_lo; ch < ch_hi; ++ch) {
         const int ns = (int)min((int64_t)kChunk, a.n - (int64_t)ch * kChunk);
         const char* qc = (const char*)(pd.Q + (int64_t)ch * kChunk);
@@ -1589,9 +1589,9 @@ __global__ __launch_bounds__(kRedoThreads) void redo_kernel(RedoArgs a) {
       double nw[kSlots / 4];
 #pragma unroll
       for (int kk = 0; kk < kSlots / 4; ++kk) nw[kk] = -w_s[4 * kk + l4][l16];
-      uint32_t oq[kSlots / 4];
+      int64_t oq[kSlots / 4];
 #pragma unroll
-      for (int kk = 0; kk < kSlots / 4; ++kk) oq[kk] = (uint32_t)((min(4 * kk + l4, q - 1) * a.n_pad + l16) * 8);
+      for (int kk = 0; kk < kSlots / 4; ++kk) oq[kk] = (min(4 * kk + l4, q - 1) * a.n_pad + l16) * 8;
       // the item's two 32-column blocks (columns past the panel's padded end
       // read the first block again; their results are not stored)
       constexpr int BB = block_bytes(PREC);
