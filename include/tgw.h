@@ -190,9 +190,12 @@ typedef struct {
 typedef struct {
   int64_t block_markers; /* markers per internal block (0 = automatic)          */
   int64_t tail_capacity; /* extreme-tail list entries (0 = 1<<20)                */
-  int32_t tile;          /* tile shape index, < 0 = default (see tgw_plan_info);
-                            also the shape of 8-bit dosage scans, where the wide
-                            shapes run the register-staged shape 2             */
+  int32_t tile;          /* tile shape index: every scan runs it, 8-bit dosages
+                            included (a shape that a precision does not have
+                            runs another one of the list).  < 0 = automatic:
+                            the autotuner's choice or the default shape, and
+                            smaller tiles (same results) for marker blocks
+                            that leave most of the GPU idle on it             */
   int32_t reserved;
 } tgw_plan_options;
 
@@ -311,7 +314,8 @@ tgw_status tgw_panel_info(const tgw_panel* panel, int64_t* n, int64_t* p, int32_
 tgw_status tgw_plan_create(const tgw_panel* const* panels, int32_t n_panels,
                            const tgw_plan_options* opts, tgw_plan** out);
 void tgw_plan_free(tgw_plan* plan);
-/* tile = chosen tile shape index; n_tiles = number of shapes;
+/* tile = chosen tile shape index (of the blocks that do not take smaller
+ * tiles, see tgw_plan_options); n_tiles = number of shapes;
  * block_markers = markers per internal block. */
 tgw_status tgw_plan_info(const tgw_plan* plan, int32_t* tile, int32_t* n_tiles, int64_t* block_markers);
 /* Tile shape idx as (markers per workgroup tile, columns per tile, waves). */
@@ -408,8 +412,9 @@ tgw_status tgw_plan_profile_read(tgw_plan* plan, void* stream, double* main_ms, 
  *   - at most 32 panels and 2^20 phenotype columns in all (TGW_ERR_SHAPE);
  *     the marker block is the largest multiple of 512 markers whose
  *     workspace fits (330,240 markers for one panel, 13,824 for 32);
- *   - tile: the tile shape index (< 0: shape 0; 8-bit dosages: shape 2);
- *     no autotuning, no hit list, no profiling;
+ *   - tile: as in tgw_plan_options (< 0: shape 0, 8-bit dosages shape 2, and
+ *     smaller tiles where they leave most of the GPU idle); no autotuning, no
+ *     hit list, no profiling;
  *   - the tail list holds 65,536 tests; d_n_tail (device, may be NULL)
  *     receives the number of tail tests the call found: above 65,536 the
  *     excess keep the table's lower bound at |t| = 40;

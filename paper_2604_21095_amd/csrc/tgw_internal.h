@@ -329,6 +329,7 @@ hipError_t launch_gemm(int idx, int prec, int mode, const GemmArgs& a, int grid,
 __host__ __device__ constexpr bool g8_supported(int prec) { return prec == kFP32 || prec == kSplit16 || prec == kSplit8; }
 // small tiles (split forms): one workgroup per tile, no resident grid; nqb: packed covariate blocks formed
 // beside the tests
+int n_small_shapes();
 TileShape small_shape(int idx);
 // the small tile of a marker block, or -1 where the plan's tile is the faster one
 int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_segs, int n_cu);

@@ -219,6 +219,8 @@ struct tgw_plan {
   int64_t tail_cap = 0;
   HitDev hits{};  // thresholded hit list of the following scans (entries NULL: off)
   int tile = 0;
+  bool pinned = false;  // the caller named the tile: every block runs on it
+  int path = -1;        // tgw_debug_set_path
   std::vector<int> grid_main;  // per tile shape
   int w_mode = kRaw;  // kRawHL for the split forms (packed hi|lo covariate operand)
   int n_cb_w = 0;     // column blocks of the Q^T g contraction
@@ -699,6 +701,7 @@ extern "C" tgw_status tgw_plan_create(const tgw_panel* const* panels, int32_t n_
     }
   }
   if (o.tile >= 0) {
+    pl->pinned = true;
     pl->tile = o.tile;
     pl->tile8 = o.tile;  // the wide shapes run shape 2 for 8-bit dosages
   } else {
@@ -791,6 +794,12 @@ struct MainPath {
 static MainPath main_path(const tgw_plan* pl, int code, int64_t nm) {
   const bool g8 = code == TGW_CODE_DOSAGE8;
   MainPath p;
+  if (pl->path >= 0) {
+    p.small = pl->path == 0 ? -1 : (pl->path - 1) % 16;
+    p.fused = pl->path > 16;
+    return p;
+  }
+  if (pl->pinned) return p;
   const int nqb = pl->n_panels == 1 && pl->w_mode == kRawHL ? hl_blocks(pl->panels[0]->cov->q) : 0;
   p.small = small_fused_shape(pl->prec, g8, nm, pl->n_cb, nqb, pl->n_segs, pl->n_cu);
   p.fused = p.small >= 0;
@@ -1358,6 +1367,7 @@ extern "C" tgw_status tgw_scan_static(const tgw_panel* const* panels, int32_t n_
   pl.w_mode = hl ? kRawHL : kRaw;
   pl.lo_int = lo_int_for(prec, panels, n_panels);
   pl.profile = false;
+  pl.pinned = tile >= 0;
   pl.tile = tile >= 0 ? tile : 0;
   pl.tile8 = tile >= 0 ? tile : 2;
   pl.grid_main.clear();
@@ -1439,6 +1449,29 @@ extern "C" tgw_status tgw_debug_contract(tgw_plan* pl, const uint8_t* d_geno, in
     a.raw_ld = lds;
     HIP_TRY(launch_gemm(tile, pl->prec, kRaw, a, g8 ? pl->grid_main8[tile] : pl->grid_main[tile], s, g8));
   }
+  return TGW_OK;
+  TGW_GUARD_END
+}
+
+extern "C" tgw_status tgw_debug_set_path(tgw_plan* pl, int32_t path) {
+  TGW_GUARD_BEGIN
+  if (!pl) return fail(TGW_ERR_INVALID_ARG, "plan is NULL");
+  if (path > 0) {
+    const int shape = (path - 1) % 16;
+    if (path > 32 || shape >= n_small_shapes()) return fail(TGW_ERR_INVALID_ARG, "no such path");
+    if (path > 16 && (pl->n_panels != 1 || pl->prec == kFP32 || pl->n_cb > small_shape(shape).wn_frags))
+      return fail(TGW_ERR_SHAPE, "Q^T g beside the tests needs one panel within a tile's columns");
+  }
+  pl->path = path < 0 ? -1 : path;
+  return TGW_OK;
+  TGW_GUARD_END
+}
+
+extern "C" tgw_status tgw_debug_path(const tgw_plan* pl, tgw_geno_code code, int64_t n_markers, int32_t* path) {
+  TGW_GUARD_BEGIN
+  if (!pl || !path) return fail(TGW_ERR_INVALID_ARG, "NULL argument");
+  const MainPath p = main_path(pl, (int)code, std::min(n_markers, pl->MB));
+  *path = p.small < 0 ? 0 : 1 + p.small + (p.fused ? 16 : 0);
   return TGW_OK;
   TGW_GUARD_END
 }

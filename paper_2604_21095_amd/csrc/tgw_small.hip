@@ -548,6 +548,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(GemmArgs a) {
 // {waves, fragments per wave, column blocks} of the compiled shapes
 static const TileShape kSmall[] = {{4, 1, 1}, {4, 2, 1}, {4, 1, 2}, {4, 2, 2}, {4, 1, 4}};
 constexpr int kNumSmall = sizeof(kSmall) / sizeof(kSmall[0]);
+int n_small_shapes() { return kNumSmall; }
 TileShape small_shape(int idx) { return kSmall[idx]; }
 
 // Cycles (at 2.4 GHz) per 64-sample chunk of one tile, measured at N = 23,000

@@ -124,6 +124,8 @@ _dbg_contract = _sig("tgw_debug_contract", ctypes.c_int, _vp, _vp, _i64, _i64, c
 _dbg_set_operand = _sig("tgw_debug_set_operand", ctypes.c_int, _vp, _vp, _i64, _vp)
 _dbg_stats = _sig("tgw_debug_marker_stats", ctypes.c_int, _vp, _vp, _i64, _i64, ctypes.c_int, _i64, _i64, _vp, _vp,
                   _vp, _vp)
+_dbg_set_path = _sig("tgw_debug_set_path", ctypes.c_int, _vp, _i32)
+_dbg_path = _sig("tgw_debug_path", ctypes.c_int, _vp, ctypes.c_int, _i64, ctypes.POINTER(_i32))
 _set_allocator = _sig("tgw_set_allocator", ctypes.c_int, _vp, _vp, _vp)
 _topk_read = _sig("tgw_topk_read", ctypes.c_int, _vp, _vp, _i32, _vp, _vp, _vp)
 _arena_create = _sig("tgw_arena_create", ctypes.c_int, _vp, ctypes.c_size_t, _pp)
@@ -532,6 +534,16 @@ class Plan:
         _check(_dbg_stats(self._h, g, nm, rb, code, m0, m1, _ptr(shift), _ptr(mean), _ptr(scale), _stream(stream)),
                "tgw_debug_marker_stats")
         return shift, mean, scale
+
+    def debug_path(self, n_markers: int, code=CODE_DOSAGE) -> int:
+        """What tests a block of n_markers markers: 0 the plan's tile, 1 + i small tile i, 17 + i the
+        same with Q^T g beside the tests."""
+        p = _i32()
+        _check(_dbg_path(self._h, code, n_markers, ctypes.byref(p)), "tgw_debug_path")
+        return p.value
+
+    def debug_set_path(self, path: int = -1):
+        _check(_dbg_set_path(self._h, path), "tgw_debug_set_path")
 
     def __del__(self, _free=_plan_free):  # bound early: module globals are gone at interpreter exit
         if getattr(self, "_h", None):
