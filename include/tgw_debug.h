@@ -55,12 +55,14 @@ tgw_status tgw_debug_marker_stats(tgw_plan* plan, const uint8_t* d_geno, int64_t
 /* Which kernel tests a marker block: 0 = the plan's tile, 1 + i = small tile
  * shape i, 17 + i = small tile shape i with Q^T g formed beside the tests (one
  * panel whose columns fit in the tile).  tgw_debug_path tells what a scan of
- * n_markers markers on this plan takes for its first block; tgw_debug_set_path
+ * n_markers markers on this plan takes for its first block (topk_k: entries of
+ * its longest top-k list, 0: none); tgw_debug_set_path
  * fixes it for the following scans (-1: as the plan chooses).  A shape that is
  * not compiled for the plan's precision and coding makes the scan fail with
  * TGW_ERR_DEVICE.  Test use only. */
 tgw_status tgw_debug_set_path(tgw_plan* plan, int32_t path);
-tgw_status tgw_debug_path(const tgw_plan* plan, tgw_geno_code code, int64_t n_markers, int32_t* path);
+tgw_status tgw_debug_path(const tgw_plan* plan, tgw_geno_code code, int64_t n_markers, int32_t topk_k,
+                          int32_t* path);
 /* A counting allocator for tgw_set_allocator: hipMalloc / hipFree, with the
  * calls and bytes recorded in the tgw_debug_alloc_counts that ctx points to
  * (updated atomically).  Test use only. */

@@ -331,11 +331,22 @@ __host__ __device__ constexpr bool g8_supported(int prec) { return prec == kFP32
 // beside the tests
 int n_small_shapes();
 TileShape small_shape(int idx);
-// the small tile of a marker block, or -1 where the plan's tile is the faster one
-int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_segs, int n_cu);
-// of a one-panel block whose Q^T g (nqb packed blocks) the same kernel forms, or -1
-int small_fused_shape(int prec, bool g8, int64_t nm, int n_cb, int nqb, int n_segs, int n_cu);
-// of the Q^T g contraction alone
+// what the choice of a marker block's tile looks at
+struct ScanShape {
+  int prec;
+  bool g8;
+  int64_t nm;
+  int n_cb, n_chunks, n_segs, seg_len, n_cu;
+  int topk_k;       // entries of the longest top-k list asked for
+  int nqb;          // packed covariate blocks of a one-panel plan in a split form, else 0
+  double wide_rel;  // time of the plan's tile over the default tile's
+};
+struct SmallChoice {
+  int shape = -1;      // < 0: the plan's tile is the faster one
+  bool fused = false;  // the same kernel forms Q^T g
+};
+SmallChoice small_choice(const ScanShape& s);
+// the small tile of the Q^T g contraction alone
 int small_q_shape(int prec, int64_t nm, int n_cb, int n_segs, int n_cu);
 const void* gemm_small_fp32_fn(int idx, int mode, bool g8);
 hipError_t launch_gemm_small(int idx, int prec, int mode, int nqb, const GemmArgs& a, hipStream_t s, bool g8);

@@ -221,6 +221,7 @@ struct tgw_plan {
   int tile = 0;
   bool pinned = false;  // the caller named the tile: every block runs on it
   int path = -1;        // tgw_debug_set_path
+  double wide_rel[2] = {1.0, 1.0};  // autotuned tile: its time over the default tile's (2-bit codes, dosages)
   std::vector<int> grid_main;  // per tile shape
   int w_mode = kRaw;  // kRawHL for the split forms (packed hi|lo covariate operand)
   int n_cb_w = 0;     // column blocks of the Q^T g contraction
@@ -791,7 +792,7 @@ struct MainPath {
   int small = -1;
   bool fused = false;
 };
-static MainPath main_path(const tgw_plan* pl, int code, int64_t nm) {
+static MainPath main_path(const tgw_plan* pl, int code, int64_t nm, int topk_k) {
   const bool g8 = code == TGW_CODE_DOSAGE8;
   MainPath p;
   if (pl->path >= 0) {
@@ -800,11 +801,29 @@ static MainPath main_path(const tgw_plan* pl, int code, int64_t nm) {
     return p;
   }
   if (pl->pinned) return p;
-  const int nqb = pl->n_panels == 1 && pl->w_mode == kRawHL ? hl_blocks(pl->panels[0]->cov->q) : 0;
-  p.small = small_fused_shape(pl->prec, g8, nm, pl->n_cb, nqb, pl->n_segs, pl->n_cu);
-  p.fused = p.small >= 0;
-  if (!p.fused) p.small = small_test_shape(pl->prec, g8, nm, pl->n_cb, pl->n_segs, pl->n_cu);
+  ScanShape s;
+  s.prec = pl->prec;
+  s.g8 = g8;
+  s.nm = nm;
+  s.n_cb = pl->n_cb;
+  s.n_chunks = pl->n_chunks;
+  s.n_segs = pl->n_segs;
+  s.seg_len = seg_chunks(pl->prec, pl->n_chunks);
+  s.n_cu = pl->n_cu;
+  s.topk_k = topk_k;
+  s.nqb = pl->n_panels == 1 && pl->w_mode == kRawHL ? hl_blocks(pl->panels[0]->cov->q) : 0;
+  s.wide_rel = pl->wide_rel[g8];
+  const SmallChoice c = small_choice(s);
+  p.small = c.shape;
+  p.fused = c.fused;
   return p;
+}
+// entries of the longest top-k list that a call fills
+static int longest_list(const tgw_plan* pl, const tgw_outputs* outs) {
+  int k = 0;
+  for (int j = 0; j < pl->n_panels; ++j)
+    if (outs[j].topk) k = std::max(k, (int)outs[j].topk_k);
+  return k;
 }
 
 // per-block preamble: integer stats, Q^T g, ||g_res||
@@ -932,9 +951,10 @@ hipError_t tgw::enqueue_scan_begin(tgw_plan* pl, const tgw_outputs* outs, hipStr
 
 hipError_t tgw::enqueue_scan_rows(tgw_plan* pl, const ScanCall& c, int64_t m_lo, int64_t m_hi, hipStream_t s) {
   hipError_t e = hipSuccess;
+  const int topk_k = longest_list(pl, c.outs);
   for (int64_t m0 = m_lo; e == hipSuccess && m0 < m_hi; m0 += pl->MB) {
     const int64_t nm = std::min(pl->MB, m_hi - m0);
-    const MainPath mp = main_path(pl, c.code, nm);
+    const MainPath mp = main_path(pl, c.code, nm, topk_k);
     e = enqueue_block_stats(pl, c, m0, nm, mp, s);
     if (e == hipSuccess) e = enqueue_main(pl, c, m0, nm, c.code == TGW_CODE_DOSAGE8 ? pl->tile8 : pl->tile, mp, s);
     if (e == hipSuccess) e = enqueue_redo(pl, c, m0, s);
@@ -1045,7 +1065,7 @@ extern "C" tgw_status tgw_plan_autotune(tgw_plan* pl, const uint8_t* d_geno, int
   HIP_TRY(hipEventCreate(&e1));
   const bool g8 = code == TGW_CODE_DOSAGE8;
   int best = g8 ? pl->tile8 : pl->tile;
-  double best_t = 1e300;
+  double best_t = 1e300, default_t = 0.0;
   hipError_t err = hipSuccess;
   for (int t = 0; t < n_tile_shapes() && err == hipSuccess; ++t) {
     if (tile_alias(t, pl->prec, g8) != t) continue;  // same kernel as an earlier shape
@@ -1058,6 +1078,7 @@ extern "C" tgw_status tgw_plan_autotune(tgw_plan* pl, const uint8_t* d_geno, int
     if (err == hipSuccess) err = hipEventSynchronize(e1);
     float ms = 0.f;
     if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
+    if (err == hipSuccess && t == tile_alias(g8 ? 2 : 0, pl->prec, g8)) default_t = ms / reps;
     if (err == hipSuccess && ms / reps < best_t) {
       best_t = ms / reps;
       best = t;
@@ -1073,6 +1094,8 @@ extern "C" tgw_status tgw_plan_autotune(tgw_plan* pl, const uint8_t* d_geno, int
     pl->tile = best;
     tune_cache_write(tune_key(pl), best);
   }
+  // the choice of small tiles compares with the default tile's time
+  if (default_t > 0.0) pl->wide_rel[g8] = best_t / default_t;
   if (best_ms) *best_ms = best_t;
   return TGW_OK;
   TGW_GUARD_END
@@ -1368,6 +1391,7 @@ extern "C" tgw_status tgw_scan_static(const tgw_panel* const* panels, int32_t n_
   pl.lo_int = lo_int_for(prec, panels, n_panels);
   pl.profile = false;
   pl.pinned = tile >= 0;
+  pl.wide_rel[0] = pl.wide_rel[1] = 1.0;
   pl.tile = tile >= 0 ? tile : 0;
   pl.tile8 = tile >= 0 ? tile : 2;
   pl.grid_main.clear();
@@ -1467,10 +1491,11 @@ extern "C" tgw_status tgw_debug_set_path(tgw_plan* pl, int32_t path) {
   TGW_GUARD_END
 }
 
-extern "C" tgw_status tgw_debug_path(const tgw_plan* pl, tgw_geno_code code, int64_t n_markers, int32_t* path) {
+extern "C" tgw_status tgw_debug_path(const tgw_plan* pl, tgw_geno_code code, int64_t n_markers, int32_t topk_k,
+                                     int32_t* path) {
   TGW_GUARD_BEGIN
   if (!pl || !path) return fail(TGW_ERR_INVALID_ARG, "NULL argument");
-  const MainPath p = main_path(pl, (int)code, std::min(n_markers, pl->MB));
+  const MainPath p = main_path(pl, (int)code, std::min(n_markers, pl->MB), topk_k);
   *path = p.small < 0 ? 0 : 1 + p.small + (p.fused ? 16 : 0);
   return TGW_OK;
   TGW_GUARD_END

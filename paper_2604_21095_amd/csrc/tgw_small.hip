@@ -563,62 +563,156 @@ constexpr int kNumSmall = sizeof(kSmall) / sizeof(kSmall[0]);
 int n_small_shapes() { return kNumSmall; }
 TileShape small_shape(int idx) { return kSmall[idx]; }
 
-// Cycles (at 2.4 GHz) per 64-sample chunk of one tile, measured at N = 23,000
-// with dense outputs: alone on its CU (one tile per CU) and per tile with two
-// to four tiles per CU; `wide` is the plan's default tile.  A block takes the
-// shape with the least ceil(tiles per CU) x cycles: the wide tile computes a
-// 32 x 32 block in 390-420 cycles (FP16 + FP8) against 480-620 here, but
-// leaves CUs idle when its tiles number less than the CUs, and in its last
-// round.
+// What a marker block costs on a tile shape, in cycles at 2.4 GHz: per round of
+// the tiles over the CUs a fixed part (prologue, epilogue) and a part per
+// 64-sample chunk; `alone` with one tile per CU at the most, `shared` per tile
+// with more.  Fitted to 1,987 scans per shape and form (dense outputs or the
+// best test: N = 500 to 65,000, 500 to 100,000 markers, 65 to 20,480
+// phenotypes), whose times it gives to 3 % (one standard deviation) from N =
+// 4,000 on.  The wide tile computes a 32 x 32 block in 240 cycles (FP16 + FP8)
+// against 330 to 460 here, but spends ten times as much on a tile's fixed part
+// and leaves CUs idle where its tiles number less than the CUs, and in its
+// last round.
 namespace {
+struct Cost {
+  double kfixed, chunk;  // thousand cycles, cycles
+};
 struct TileCost {
-  int wide, alone[kNumSmall], shared[kNumSmall];
+  Cost wide, alone[kNumSmall], shared[kNumSmall];
 };
 const TileCost& tile_cost(int prec, bool g8) {
-  static const TileCost f8 = {6200, {907, 1500, 1444, 2437, 2378}, {640, 1210, 1100, 1940, 1910}};
-  static const TileCost f8_g8 = {9800, {1295, 2619, 1827, 3369, 2494}, {1190, 2220, 1555, 2950, 2230}};
-  static const TileCost f16 = {7950, {864, 1419, 1617, 2488, 2904}, {730, 1280, 1335, 2255, 2490}};
-  static const TileCost f16_g8 = {10900, {1190, 2454, 1894, 3649, 3211}, {1160, 2075, 1760, 3100, 2850}};
-  static const TileCost bf16 = {7540, {877, 1376, 1604, 2404, 2888}, {720, 1260, 1275, 2200, 2420}};
-  static const TileCost fp32 = {41900, {4803, 8678, 8113, 14292, 12862}, {3734, 7097, 6223, 11933, 10726}};
-  return prec == kSplit8 ? (g8 ? f8_g8 : f8) : prec == kSplit16 ? (g8 ? f16_g8 : f16) : prec == kSplit ? bf16 : fp32;
+  static const TileCost f8 = {{165, 3730}, {{0, 680}, {8, 1170}, {11, 1030}, {32, 2010}, {26, 1740}},
+                              {{2, 460}, {6, 900}, {7, 800}, {14, 1330}, {14, 1330}}};
+  static const TileCost f8_g8 = {{140, 8600}, {{0, 1110}, {12, 2050}, {12, 1380}, {32, 2600}, {26, 1860}},
+                                 {{2, 950}, {5, 1910}, {5, 1240}, {18, 2300}, {16, 1790}}};
+  static const TileCost f16 = {{165, 5020}, {{0, 730}, {11, 1080}, {10, 1250}, {30, 1820}, {24, 2270}},
+                               {{2, 570}, {4, 950}, {6, 1020}, {10, 1600}, {12, 1880}}};
+  static const TileCost f16_g8 = {{220, 9240}, {{0, 1250}, {10, 2030}, {10, 1740}, {30, 2620}, {26, 2830}},
+                                  {{4, 900}, {8, 1710}, {6, 1420}, {13, 2380}, {16, 2340}}};
+  static const TileCost bf16 = {{165, 5010}, {{0, 740}, {8, 1100}, {9, 1260}, {29, 1840}, {24, 2270}},
+                                {{2, 570}, {4, 940}, {4, 1010}, {12, 1600}, {11, 1860}}};
+  static const TileCost fp32 = {{105, 43700}, {{5, 2960}, {6, 6650}, {0, 6460}, {20, 12310}, {24, 10910}},
+                                {{0, 3150}, {0, 6350}, {4, 5980}, {6, 11550}, {16, 10610}}};
+  static const TileCost fp32_g8 = {{110, 41200}, {{2, 2800}, {12, 6000}, {6, 6350}, {28, 11640}, {22, 10940}},
+                                   {{0, 2760}, {0, 5610}, {8, 5530}, {12, 10770}, {29, 9660}}};
+  if (prec == kFP32) return g8 ? fp32_g8 : fp32;
+  return prec == kSplit8 ? (g8 ? f8_g8 : f8) : prec == kSplit16 ? (g8 ? f16_g8 : f16) : bf16;
 }
-int64_t rounds(int64_t nm, int n_cb, const TileShape& t, int n_cu, int n_segs = 1) {
-  const int64_t tiles = ((nm + t.tm() - 1) / t.tm()) * ((n_cb + t.wn_frags - 1) / t.wn_frags);
-  return (tiles * n_segs + n_cu - 1) / n_cu;
+int64_t n_tiles(int64_t nm, int n_cb, const TileShape& t) {
+  return (nm + t.tm() - 1) / t.tm() * ((n_cb + t.wn_frags - 1) / t.wn_frags);
+}
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+constexpr TileShape kWide{4, 4, 4};
+constexpr double kSegFlush = 20e3;  // adding a segment to the sums in memory
+
+double wide_cycles(const ScanShape& s) {
+  const Cost& c = tile_cost(s.prec, s.g8).wide;
+  return s.wide_rel * (double)ceil_div(n_tiles(s.nm, s.n_cb, kWide), s.n_cu) *
+         (1e3 * c.kfixed + s.n_chunks * c.chunk + (s.n_segs - 1) * kSegFlush);
+}
+double small_cycles(const ScanShape& s, int i) {
+  const TileCost& c = tile_cost(s.prec, s.g8);
+  const int64_t tiles = n_tiles(s.nm, s.n_cb, kSmall[i]);
+  const double one = 1e3 * c.alone[i].kfixed + std::min(s.seg_len, s.n_chunks) * c.alone[i].chunk;
+  const int64_t wgs = tiles * s.n_segs;
+  if (wgs <= s.n_cu) return one;
+  double chunks = (double)ceil_div(wgs, s.n_cu) * s.n_chunks;  // of the fullest CU
+  if (s.n_segs > 1) {  // the last segments fill up the CUs that have fewer whole ones
+    const int64_t whole = tiles * (s.n_segs - 1);
+    chunks = std::max((double)ceil_div(whole, s.n_cu) * s.seg_len, (double)tiles * s.n_chunks / s.n_cu);
+  }
+  return std::max(one, ceil_div(wgs, s.n_cu) * 1e3 * c.shared[i].kfixed + chunks * c.shared[i].chunk);
+}
+
+// Filling top-k lists: microseconds per list entry that a shape takes more (or
+// less) than the wide tile.  Every wave runs the serial insertions of its own
+// rows, column block by column block: few columns per wave are the faster ones
+// (500 markers x 2,000 phenotypes, k = 50: 512 x 128 tiles 5.4 ms, 256 x 32
+// 0.9, 128 x 32 0.7).  But each wave starts on the list as it stands, so many
+// waves with few rows each insert what others displace (one phenotype, 100,000
+// markers, k = 50, N = 500: 1.0 ms on wide tiles, 1.6 on 256 x 32, 2.2 on 128 x
+// 32), most of all in one burst, where the contraction is short.  The
+// register-staged default tiles of FP32 and of 8-bit dosages in the FP16 split
+// have half the rows per wave.  With these terms, of 2,225 scans three are more
+// than 5 % and eleven more than 2 % slower than on the wide tile (14 % at the
+// most); without them up to 2.2 times.
+double insert_us(const ScanShape& s, int i) {
+  const double m = (double)s.nm, p = 32.0 * s.n_cb;
+  const bool half = s.prec == kFP32 || (s.prec == kSplit16 && s.g8);
+  if (s.n_cb <= 2) {
+    double narrow;  // 256 x 32
+    if (half)
+      narrow = 0.0;
+    else if (s.n_cb == 2)
+      narrow = 1.5e-4 * m - 5.0;
+    else
+      narrow = 1.3e-4 * m * (n_tiles(s.nm, 1, kSmall[1]) > s.n_cu ? std::max(0.0, 1.0 - s.n_chunks / 128.0) : 1.0) +
+               (m > 15000 ? 7.0 : 0.0);
+    if (i == 1) return narrow;
+    if (s.n_cb == 1) return narrow + std::min(5e-4 * m, 20.0) - 1.5;
+    return s.prec == kFP32 ? narrow : narrow + std::min(4e-4 * m, 16.0) - 4.0;
+  }
+  double gain = m <= 1500 ? 60.0 : 25.0;
+  if (s.n_cb == 3) gain *= 0.6;
+  if (half) gain = m > 1500 ? 15.0 : p < 8000 ? 25.0 : 0.0;
+  const double rounds = p >= 4000 && s.n_chunks < 64 ? 12.0 * (ceil_div(n_tiles(s.nm, s.n_cb, kWide), s.n_cu) - 1) : 0.0;
+  if (i == 1) return rounds - gain;
+  if (i == 0)
+    return rounds - gain + (p >= 3000 ? 2e-3 * p : m >= 1000 && s.n_chunks < 32 ? 6.0 : 0.0) - (m < 1000 ? 8.0 : 0.0);
+  double t = rounds - 0.6 * gain;  // 256 x 64
+  if (i != 3) t += (s.n_chunks < 128 ? 5e-3 : 2e-3) * std::max(0.0, p - 4000.0);
+  if (i == 4 && m > 8000) t += 10.0;
+  return t;
 }
 }  // namespace
-
-int small_test_shape(int prec, bool g8, int64_t nm, int n_cb, int n_segs, int n_cu) {
-  const TileCost& c = tile_cost(prec, g8);
-  int64_t best = rounds(nm, n_cb, TileShape{4, 4, 4}, n_cu) * c.wide * n_segs;
-  int pick = -1;
-  for (int i = 0; i < kNumSmall; ++i) {
-    const int64_t r = rounds(nm, n_cb, kSmall[i], n_cu, n_segs);
-    const int64_t t = r <= 1 ? c.alone[i] : r * c.shared[i];
-    if (t < best) best = t, pick = i;
-  }
-  return pick;
-}
 
 // Q^T g beside the tests saves the second decode of the genotypes (a third
 // of the two kernels' time) and two launches; the panel's columns then have
 // to fit in one tile.  One column block and one covariate block: two
 // fragments per wave halve the operand reads (1,450 cycles per tile against
-// 2 x 830), but 256-row tiles leave more of the last round empty.
-int small_fused_shape(int prec, bool g8, int64_t nm, int n_cb, int nqb, int n_segs, int n_cu) {
-  if (prec == kFP32 || nqb < 1 || n_cb > 2) return -1;
-  if (n_cb == 2) return 2;
-  if (nqb > 1 || g8) return 0;
-  const int64_t r0 = rounds(nm, n_cb, kSmall[0], n_cu, n_segs), r1 = rounds(nm, n_cb, kSmall[1], n_cu, n_segs);
+// 2 x 830), but 256-row tiles leave more of the last round empty.  Of 592
+// scans (dense outputs or the best test, N = 500 to 60,000, up to 100,000
+// markers) all take at most 0.9 of the wide tile's time.
+static int small_fused_shape(const ScanShape& s) {
+  if (s.n_cb == 2) return 2;
+  if (s.nqb > 1 || s.g8) return 0;
+  const int64_t r0 = ceil_div(n_tiles(s.nm, 1, kSmall[0]) * s.n_segs, s.n_cu);
+  const int64_t r1 = ceil_div(n_tiles(s.nm, 1, kSmall[1]) * s.n_segs, s.n_cu);
   return r1 * (r1 > 1 ? 1450 : 1720) < r0 * (r0 > 1 ? 830 : 1000) ? 1 : 0;
+}
+
+// A small tile has to be 1 % faster by the estimate.  FP16 + FP8, N = 60,000,
+// 10,000 markers x 1,000 phenotypes: 2.28 ms on the 128 x 64 tiles, 2.00 on the
+// wide ones.
+SmallChoice small_choice(const ScanShape& s) {
+  const bool fusable = s.prec != kFP32 && s.nqb > 0 && s.n_cb <= 2;
+  if (fusable && s.topk_k == 0) return SmallChoice{small_fused_shape(s), true};
+  double wide = wide_cycles(s);
+  SmallChoice best;
+  double least = 0.0;
+  auto offer = [&](int i, bool fused, double t) {
+    if (best.shape < 0 || t < least) least = t, best = SmallChoice{i, fused};
+  };
+  const bool lists = s.topk_k > 0, one_block = fusable && s.n_cb == 1;
+  // the separate Q^T g that a fused shape saves
+  const double q = one_block ? 0.8 * s.nqb * std::min(small_cycles(s, 0), small_cycles(s, 1)) : 0.0;
+  wide += q;
+  for (int i = 0; i < kNumSmall; ++i) {
+    if (lists && s.n_cb <= 2 && i > 1) break;
+    const double t = small_cycles(s, i) + (lists ? 2400.0 * s.topk_k * insert_us(s, i) : 0.0);
+    if (one_block && (i == 0 || (s.nqb == 1 && !s.g8)))
+      offer(i, true, t);
+    else
+      offer(i, false, t + q);
+  }
+  return least < 0.99 * wide ? best : SmallChoice{};
 }
 
 // 256-row tiles once they fill the GPU (100,000 markers, N = 23,000: 0.21 ms
 // against 0.25 ms on 128-row ones), else 128-row ones (4,096 markers, N =
 // 500,001 in one segment: 2.0 against 3.2 ms)
 int small_q_shape(int prec, int64_t nm, int n_cb, int n_segs, int n_cu) {
-  return prec != kFP32 && rounds(nm, n_cb, kSmall[1], n_cu, n_segs) > 1 ? 1 : 0;
+  return prec != kFP32 && n_tiles(nm, n_cb, kSmall[1]) * n_segs > n_cu ? 1 : 0;
 }
 
 template <int PREC, int NQB, bool G8, int PH>

@@ -125,7 +125,7 @@ _dbg_set_operand = _sig("tgw_debug_set_operand", ctypes.c_int, _vp, _vp, _i64, _
 _dbg_stats = _sig("tgw_debug_marker_stats", ctypes.c_int, _vp, _vp, _i64, _i64, ctypes.c_int, _i64, _i64, _vp, _vp,
                   _vp, _vp)
 _dbg_set_path = _sig("tgw_debug_set_path", ctypes.c_int, _vp, _i32)
-_dbg_path = _sig("tgw_debug_path", ctypes.c_int, _vp, ctypes.c_int, _i64, ctypes.POINTER(_i32))
+_dbg_path = _sig("tgw_debug_path", ctypes.c_int, _vp, ctypes.c_int, _i64, _i32, ctypes.POINTER(_i32))
 _set_allocator = _sig("tgw_set_allocator", ctypes.c_int, _vp, _vp, _vp)
 _topk_read = _sig("tgw_topk_read", ctypes.c_int, _vp, _vp, _i32, _vp, _vp, _vp)
 _arena_create = _sig("tgw_arena_create", ctypes.c_int, _vp, ctypes.c_size_t, _pp)
@@ -535,11 +535,11 @@ class Plan:
                "tgw_debug_marker_stats")
         return shift, mean, scale
 
-    def debug_path(self, n_markers: int, code=CODE_DOSAGE) -> int:
-        """What tests a block of n_markers markers: 0 the plan's tile, 1 + i small tile i, 17 + i the
+    def debug_path(self, n_markers: int, code=CODE_DOSAGE, topk: int = 0) -> int:
+        """What tests a block of n_markers markers (filling top-k lists of topk entries): 0 the plan's tile, 1 + i small tile i, 17 + i the
         same with Q^T g beside the tests."""
         p = _i32()
-        _check(_dbg_path(self._h, code, n_markers, ctypes.byref(p)), "tgw_debug_path")
+        _check(_dbg_path(self._h, code, n_markers, topk, ctypes.byref(p)), "tgw_debug_path")
         return p.value
 
     def debug_set_path(self, path: int = -1):

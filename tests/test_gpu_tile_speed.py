@@ -45,7 +45,7 @@ def _ratio(tgw, precision, code, n, m, p, topk):
     reps = max(2, min(50, int(5.0 / time_of(plans[1], 2))))
     times = [[time_of(plan, reps) for plan in plans] for _ in range(7)]
     auto, named = (statistics.median(t[i] for t in times) for i in (0, 1))
-    say(f"case: {precision} {code} n={n} m={m} p={p} topk={topk}: path {plans[0].debug_path(m, c)}, "
+    say(f"case: {precision} {code} n={n} m={m} p={p} topk={topk}: path {plans[0].debug_path(m, c, topk)}, "
         f"{auto * 1e3:.0f} us, default tile {named * 1e3:.0f} us")
     return auto / named
 
@@ -57,3 +57,19 @@ def _ratio(tgw, precision, code, n, m, p, topk):
 ])
 def test_uneven_segments(tgw, precision, code, n, m, p):
     assert _ratio(tgw, precision, code, n, m, p, 0) < 1.15
+
+
+@pytest.mark.parametrize("precision,code,n,m,p,topk", [
+    ("split8", "dosage", 500, 30_000, 1, 50),     # many waves at one list
+    ("split", "dosage", 500, 30_000, 20, 10),
+    ("split16", "dosage", 500, 100_000, 40, 50),
+    ("fp32", "dosage", 1000, 2000, 20_480, 10),   # short sums, long lists
+    ("split8", "dosage", 8000, 500, 20_480, 10),
+    ("split16", "dosage8", 1500, 2000, 5000, 50),
+    ("split16", "dosage8", 1000, 1301, 18_643, 10),
+    ("split8", "dosage8", 500, 60_000, 300, 10),
+    ("split8", "dosage", 60_000, 10_000, 1000, 0),  # a full round of wide tiles, long sums
+    ("fp32", "dosage8", 1000, 3000, 2000, 0),
+])
+def test_outputs_and_lengths(tgw, precision, code, n, m, p, topk):
+    assert _ratio(tgw, precision, code, n, m, p, topk) < 1.15
