@@ -271,8 +271,8 @@ constexpr int kQrGrid = 128;
 constexpr int kQrScratch = kQrGrid * kSlots + 2 * kSlots;
 hipError_t launch_qr(const double* C, int64_t ldc, int64_t n, int64_t n_pad, int q, double* X, double* Q,
                      double* rdiag, double* scratch, int32_t* flags, hipStream_t s);
-// the same Q and the Q^T g operands by Cholesky, or flags[2] = 1 (Q unset) where X is too ill-conditioned
-size_t gram_scratch_doubles(int64_t n_pad);
+// the same Q and the Q^T g operands by Cholesky, or flags[2] = 1 (Q and operands unset) where X is too
+// ill-conditioned
 hipError_t launch_gram_qr(const double* C, int64_t ldc, int64_t n, int64_t n_pad, int q, double* Q1, double* Q,
                           double* scratch, int32_t* flags, void* wop_fp32, void* const* wop_hl, hipStream_t s);
 hipError_t launch_cov_operands(const double* Q, int64_t n, int64_t n_pad, int q, void* wop_fp32,

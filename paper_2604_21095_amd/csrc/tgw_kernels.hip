@@ -3025,9 +3025,6 @@ hipError_t launch_qr(const double* C, int64_t ldc, int64_t n, int64_t n_pad, int
 static int gram_waves(int64_t n_pad) {  // about four chunks a wave, at most 256 waves
   return (int)std::max<int64_t>(1, std::min<int64_t>(256, n_pad / kChunk / 4));
 }
-size_t gram_scratch_doubles(int64_t n_pad) {
-  return (size_t)gram_waves(n_pad) * kGramTiles * 256 + 2 * kSlots * kSlots + kSlots;
-}
 
 hipError_t launch_gram_qr(const double* C, int64_t ldc, int64_t n, int64_t n_pad, int q, double* Q1, double* Q,
                           double* scratch, int32_t* flags, void* wop_fp32, void* const* wop_hl, hipStream_t s) {
@@ -3040,7 +3037,10 @@ hipError_t launch_gram_qr(const double* C, int64_t ldc, int64_t n, int64_t n_pad
   a.q = q;
   a.waves = gram_waves(n_pad);
   a.coef = scratch;
-  a.part = scratch + 2 * kSlots * kSlots + kSlots;
+  static_assert(2 * kSlots * kSlots + kSlots <= kQrScratch, "the factors fit in the QR's scratch");
+  // the waves' tiles (6 KiB for every four chunks, or one wave's) lie in the
+  // FP32 operand (8 KiB per chunk), which is written when they have been read
+  a.part = (double*)wop_fp32;
   a.Q1 = Q1;
   a.Q = Q;
   a.flags = flags;

@@ -328,7 +328,7 @@ extern "C" tgw_status tgw_fit_covariates(int64_t n_samples, int32_t n_cov, const
   hipError_t e = dmalloc(A, &cov->Q, (size_t)cov->q * cov->n_pad, s);
   if (e == hipSuccess) e = dmalloc(A, &X, (size_t)cov->q * cov->n_pad, s);
   if (e == hipSuccess) e = dmalloc(A, &rdiag, (size_t)cov->q, s);
-  if (e == hipSuccess) e = dmalloc(A, &qrs, std::max((size_t)kQrScratch, gram_scratch_doubles(cov->n_pad)), s);
+  if (e == hipSuccess) e = dmalloc(A, &qrs, (size_t)kQrScratch, s);
   if (e == hipSuccess) e = dmalloc(A, &flags, 3, s);
   if (e == hipSuccess) e = dev_alloc(A, &cov->wop_fp32, (size_t)cov->n_chunks * kBlockBytes, s);
   for (int k : {(int)kSplit, (int)kSplit16})
