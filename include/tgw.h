@@ -356,7 +356,8 @@ tgw_status tgw_plan_autotune(tgw_plan* plan, const uint8_t* d_geno, int64_t n_ma
  * split forms; the FP16 hi + FP8 lo form orders its FP32 accumulation by a
  * marker's row in the 512-marker tile).  Above 65,536 samples the FP16 forms
  * add up to eight segments of the samples in order, each accumulated in FP32
- * from zero; the segments follow from the sample count alone.
+ * from zero; the segments follow from the sample count alone (a plan whose
+ * allocator has not even 2 MiB left for their sums takes one segment).
  * Asynchronous: enqueues kernels on `stream`, allocates nothing and does not
  * synchronize; capturable in a HIP graph.  The plan's workspace is reused, so
  * calls with the same plan must not run concurrently on different streams.

@@ -675,12 +675,19 @@ extern "C" tgw_status tgw_plan_create(const tgw_panel* const* panels, int32_t n_
   if (e == hipSuccess) e = dmalloc(pl->mem, &pl->tail_entries, (size_t)pl->tail_cap);
   if (e == hipSuccess) e = dmalloc(pl->mem, &pl->tail_count, 1);
   pl->n_segs = n_segments(pl->prec, pl->n_chunks);
-  if (e == hipSuccess && pl->n_segs > 1) {  // with less room than a scan wants it takes more and smaller steps
+  if (e == hipSuccess && pl->n_segs > 1) {
+    // with less room than a scan wants it takes more and smaller steps, with
+    // none a single run over the samples
     for (int64_t want = seg_part_bytes(pl->n_segs, pl->n_cu);; want = std::max(kSegPartLeast, want / 2)) {
-      e = dev_alloc(pl->mem, (void**)&pl->part, (size_t)want, nullptr);
       pl->part_bytes = want;
-      if (e == hipSuccess || want == kSegPartLeast) break;
+      if (dev_alloc(pl->mem, (void**)&pl->part, (size_t)want, nullptr) == hipSuccess) break;
+      pl->part = nullptr;
       (void)hipGetLastError();
+      if (want == kSegPartLeast) {
+        pl->n_segs = 1;
+        pl->part_bytes = 0;
+        break;
+      }
     }
   }
   if (e == hipSuccess) e = hipMemcpy(pl->d_cb_main, cbm.data(), cbm.size() * sizeof(ColBlock), hipMemcpyHostToDevice);
@@ -808,7 +815,7 @@ static MainPath main_path(const tgw_plan* pl, int code, int64_t nm, int topk_k) 
   s.n_cb = pl->n_cb;
   s.n_chunks = pl->n_chunks;
   s.n_segs = pl->n_segs;
-  s.seg_len = seg_chunks(pl->prec, pl->n_chunks);
+  s.seg_len = pl->n_segs > 1 ? seg_chunks(pl->prec, pl->n_chunks) : pl->n_chunks;
   s.n_cu = pl->n_cu;
   s.topk_k = topk_k;
   s.nqb = pl->n_panels == 1 && pl->w_mode == kRawHL ? hl_blocks(pl->panels[0]->cov->q) : 0;

@@ -46,3 +46,44 @@ def test_fit_asks_for_no_more_than_its_buffers(tgw, kind, n, k):
     assert torch.equal(cov.Q(), want)
     del cov
     arena.close()
+
+
+@pytest.mark.parametrize("precision,p", [("split8", 40), ("split16", 300)])
+def test_long_cohort_plan_without_room_for_segments(tgw, precision, p):
+    """A plan for 65,600 samples where one for 65,536 fits exactly: it scans
+    all the same, in one run over the samples."""
+    say(f"case: plan in exact memory {precision} p={p}")
+    k, m = 5, 700
+
+    def inputs(n):
+        g = torch.Generator(device="cuda").manual_seed(3)
+        geno = torch.randint(0, 256, (m, (n + 63) // 64 * 16), generator=g, device="cuda", dtype=torch.uint8)
+        C = torch.randn((k, n), generator=g, device="cuda", dtype=torch.float64).t()
+        Y = torch.randn((p, n), generator=g, device="cuda").t()
+        return geno, tgw.prepare_phenotypes(tgw.fit_covariates(C), Y, precision)
+
+    def plan_in(arena, panel):
+        arena.register()
+        try:
+            return tgw.Plan([panel], block_markers=512, tail_capacity=1024)
+        finally:
+            tgw.set_allocator()
+
+    big = tgw.torch_arena(256 << 20)
+    short = plan_in(big, inputs(65_536)[1])
+    need = big.info().peak
+    del short
+    big.close()
+    geno, panel = inputs(65_600)
+    want = tgw.scan(tgw.Plan([panel]), geno)[0]
+    arena = tgw.torch_arena(need)
+    plan = plan_in(arena, panel)
+    assert arena.info().n_failed >= 1 and arena.info().in_use == need
+    got = tgw.make_outputs([p], m)
+    plan.scan(geno, got)
+    plan.check()
+    # both take under n / 16 FP32 steps of half an ulp, of random sign, on partial sums of under 4 sqrt(n)
+    assert (got[0]["r"] - want["r"]).abs().max() < 4e-6
+    assert torch.isfinite(got[0]["nlog10p"]).float().mean() > 0.9
+    del plan
+    arena.close()
