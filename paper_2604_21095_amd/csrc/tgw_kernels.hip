@@ -732,9 +732,10 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const void* __restri
 //   A: sums of v = y - y_0, v^2 and Q^T v (y_0: the column's first sample,
 //      so that offsets cancel; Q^T of a constant is that constant times
 //      n Q_0 in slot 0, Q_0 being constant, and 0 in the others)
-//   B: ||y_res||^2 explicitly, only for columns that the covariates nearly
-//      explain (||y_c||^2 - ||Q^T y_c||^2 below 1e-4 ||y_c||^2, where the
-//      difference is still good to 1e-12)
+//   B: ||y_res||^2 explicitly, only for columns where ||y_c||^2 - ||Q^T y_c||^2
+//      is below 1e-4 of the sum of v^2 it is a difference from (there still
+//      good to 1e-12): columns that the covariates nearly explain, or whose
+//      first sample is far off the others
 //   C: FP16 + FP8 form: the largest |lo| term
 //   D: the operand, and the sums of what it holds
 // N = 23,000, K = 10, FP16 + FP8 form: P = 2,048 (FP64 input) 1,010 -> 510 us,
@@ -925,7 +926,8 @@ __device__ __forceinline__ PrepColumn prep_column(const PrepArgs& a, int64_t c, 
   const double d = a.sums[kPrepSlotV * nc + c] / (double)a.n;
   p.mean = y0 + d;
   *delta = d;
-  p.yc2 = fmax(a.sums[kPrepSlotVV * nc + c] - (double)a.n * d * d, 0.0);
+  const double v2 = a.sums[kPrepSlotVV * nc + c];
+  p.yc2 = fmax(v2 - (double)a.n * d * d, 0.0);
   double s = p.yc2;
 #pragma unroll 8
   for (int k = 0; k < a.q; ++k) {
@@ -933,7 +935,7 @@ __device__ __forceinline__ PrepColumn prep_column(const PrepArgs& a, int64_t c, 
     s -= t * t;
   }
   p.r2 = s;
-  p.direct = s > 1e-4 * p.yc2;
+  p.direct = s > 1e-4 * v2;
   return p;
 }
 
