@@ -181,32 +181,37 @@ __global__ __launch_bounds__(kQrThreads) void qr_coef_kernel(double* X, int64_t 
                                                              const double* __restrict__ part, double* rdiag,
                                                              double* fv, double* vtv) {
   __shared__ double ps[kQrGrid * kSlots];
-  __shared__ double dv[kSlots];
+  __shared__ double dv[kSlots], row[kSlots];
+  const int k = threadIdx.x;
+  const bool mine = k >= j && k < q;
+  if (forward && mine) row[k] = X[(int64_t)k * n_pad + j];
   for (int idx = threadIdx.x; idx < kQrGrid * kSlots; idx += kQrThreads) ps[idx] = part[idx];
   __syncthreads();
-  const int k = threadIdx.x;
-  if (k >= j && k < q) {
+  if (mine) {
     double s = 0.0;
+#pragma unroll 16
     for (int b = 0; b < kQrGrid; ++b) s += ps[b * kSlots + k];
     dv[k] = s;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  if (!mine) return;
   if (forward) {
-    double* xj = X + (int64_t)j * n_pad;
-    const double xjj = xj[j];
+    const double xjj = row[j];
     const double below = dv[j];
     const double nrm = sqrt(xjj * xjj + below);
     const double alpha = xjj > 0.0 ? -nrm : nrm;
     const double v0 = xjj - alpha;
     const double t = below + v0 * v0;
-    xj[j] = v0;
-    rdiag[j] = alpha;
-    vtv[j] = t;
-    for (int c = j + 1; c < q; ++c) fv[c] = t > 0.0 ? 2.0 * (dv[c] + v0 * X[(int64_t)c * n_pad + j]) / t : 0.0;
+    if (k == j) {
+      X[(int64_t)j * n_pad + j] = v0;
+      rdiag[j] = alpha;
+      vtv[j] = t;
+    } else {
+      fv[k] = t > 0.0 ? 2.0 * (dv[k] + v0 * row[k]) / t : 0.0;
+    }
   } else {
     const double t = vtv[j];
-    for (int c = j; c < q; ++c) fv[c] = t > 0.0 ? 2.0 * dv[c] / t : 0.0;
+    fv[k] = t > 0.0 ? 2.0 * dv[k] / t : 0.0;
   }
 }
 
@@ -251,31 +256,66 @@ __global__ void qr_rank_kernel(const double* rdiag, int q, int32_t* flags) {
 // block when q <= 16, else two): slot k goes to block k / 16, its hi part in
 // column k % 16 and its lo part in column k % 16 + 16 of the hi half, the lo
 // half zero, so that one matrix-core pass forms both products.
-__global__ void cov_operand_kernel(const double* __restrict__ Q, int64_t n, int64_t n_pad, int q, void* wop_fp32,
-                                   void* hl_split, void* hl_split16) {
-  const int n_chunks = (int)(n_pad / kChunk);
-  const int64_t total = n_pad * kColBlock;
-  for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = idx / kColBlock;
-    const int k = (int)(idx % kColBlock);
-    const double v = (k >= 1 && k < q && i < n) ? Q[(int64_t)k * n_pad + i] : 0.0;
-    double st;
-    store_operand(wop_fp32, kFP32, k, i, n_chunks, v, &st);
-    if (k < hl_blocks(q) * kHLSlots) {
-      const int64_t ch = 32 * (k / kHLSlots) + k % kHLSlots;  // hi column; lo column ch + 16
+// the Q^T g operands of samples 16 b .. 16 b + 15 of chunk ch and slots 16 t + l16
+// (q[i]: sample 4 i + l4 of slot 16 t + l16): slot k >= 1 <- Q[:, k], slot 0 and
+// slots >= q are zero
+__device__ __forceinline__ void cov_operand_store(float* wop_fp32, char* const (&wop_hl)[2], int n_slots, int n_chunks,
+                                                  int ch, int b, int t, int l16, int l4, f64x4 q) {
+  const int k = 16 * t + l16;
+  double v[4];
 #pragma unroll
-      for (int f = 0; f < 2; ++f) {
-        uint16_t* p = (uint16_t*)(f == 0 ? hl_split : hl_split16);
-        uint32_t hb, lb;
-        split_parts(f == 0 ? kSplit : kSplit16, v, &hb, &lb);
-        p[operand_index_split(ch, i, n_chunks, 0)] = (uint16_t)hb;
-        p[operand_index_split(ch + kHLSlots, i, n_chunks, 0)] = (uint16_t)lb;
-        p[operand_index_split(ch, i, n_chunks, 1)] = 0;
-        p[operand_index_split(ch + kHLSlots, i, n_chunks, 1)] = 0;
-      }
+  for (int i = 0; i < 4; ++i) v[i] = k >= 1 && k < n_slots ? q[i] : 0.0;
+  // packed block t: hi part in column l16, lo part in column l16 + 16 (of its
+  // first half; the second half is never read), dword l4 of step j = 2 (b & 1)
+  // + (i & 1) holding samples i and i + 2
+  if (t < hl_blocks(n_slots)) {
+    const int64_t at = ((int64_t)t * n_chunks + ch) * kBlockBytes + 2 * (b & 1) * 1024 + (b >> 1) * 512 + l16 * 16 + 4 * l4;
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      uint32_t hb[4], lb[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) split_parts(f == 0 ? kSplit : kSplit16, v[i], &hb[i], &lb[i]);
+      char* p = wop_hl[f] + at;
+      gstore(p, hb[0] | (hb[2] << 16));
+      gstore(p + 1024, hb[1] | (hb[3] << 16));
+      gstore(p + 256, lb[0] | (lb[2] << 16));
+      gstore(p + 1024 + 256, lb[1] | (lb[3] << 16));
     }
   }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    wop_fp32[(int64_t)ch * 2048 + (4 * (b & 1) + i) * 256 + (32 * (b >> 1) + k) * 4 + l4] = (float)v[i];
+}
+
+struct CovOperandArgs {
+  const double* Q;
+  int64_t n_pad;
+  int q;
+  float* wop_fp32;
+  char* wop_hl[2];  // BF16 split, FP16 split
+};
+// the operands of a Q that is in memory: one workgroup per chunk, a wave per 16 samples
+__global__ __launch_bounds__(256) void cov_operand_kernel(CovOperandArgs a) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+  const int ch = blockIdx.x, b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int k = 16 * t + l16;
+    f64x4 v = {0.0, 0.0, 0.0, 0.0};
+    if (k < a.q) {
+      const double* q = a.Q + (int64_t)k * a.n_pad + (int64_t)ch * kChunk + 16 * b + l4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = q[4 * i];
+    }
+    cov_operand_store(a.wop_fp32, a.wop_hl, a.q, (int)(a.n_pad / kChunk), ch, b, t, l16, l4, v);
+  }
+}
+
+// Q of the intercept alone: -1 / sqrt(n), the sign as of the Householder QR
+__global__ __launch_bounds__(256) void intercept_kernel(double* Q, int64_t n, int64_t n_pad) {
+  const double v = -1.0 / sqrt((double)n);
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_pad; i += (int64_t)gridDim.x * blockDim.x)
+    Q[i] = i < n ? v : 0.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -333,7 +373,7 @@ __global__ __launch_bounds__(64) void gram_kernel(GramArgs a) {
   const int w = blockIdx.x;
   const int nch = (int)(a.n_pad / kChunk);
   const int ch_lo = (int)((int64_t)nch * w / gridDim.x), ch_hi = (int)((int64_t)nch * (w + 1) / gridDim.x);
-  if (PASS == 2 && a.flags[2]) return;
+  if (PASS > 0 && a.flags[2]) return;
   constexpr int KK = 4 * NT;
   double m[NT][KK];  // this pass's factor: element (4 kk + l4, 16 t + l16)
   if constexpr (PASS > 0) {
@@ -378,38 +418,10 @@ __global__ __launch_bounds__(64) void gram_kernel(GramArgs a) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) out[(int64_t)k * a.n_pad + s0 + 4 * i + l4] = d[t][i];
           }
-          if constexpr (PASS == 2) {
-            // operand columns: slot k >= 1 <- Q[:, k]; slot 0 and slots >= q are zero
-            double v[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = k >= 1 && k < a.q ? d[t][i] : 0.0;
-            // packed block t: hi part in column l16, lo part in column l16 + 16
-            // (of its first half; the second half is never read), dword l4 of
-            // step j = 2 (b & 1) + (i & 1) holding samples i and i + 2
-            if (t < hl_blocks(a.q)) {
-              const int64_t at = ((int64_t)t * nch + ch) * kBlockBytes + 2 * (b & 1) * 1024 + (b >> 1) * 512 + l16 * 16 + 4 * l4;
-#pragma unroll
-              for (int f = 0; f < 2; ++f) {
-                uint32_t hb[4], lb[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) split_parts(f == 0 ? kSplit : kSplit16, v[i], &hb[i], &lb[i]);
-                char* p = a.wop_hl[f] + at;
-                gstore(p, hb[0] | (hb[2] << 16));
-                gstore(p + 1024, hb[1] | (hb[3] << 16));
-                gstore(p + 256, lb[0] | (lb[2] << 16));
-                gstore(p + 1024 + 256, lb[1] | (lb[3] << 16));
-              }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              a.wop_fp32[(int64_t)ch * 2048 + (4 * (b & 1) + i) * 256 + (32 * (b >> 1) + k) * 4 + l4] = (float)v[i];
-          }
+          if constexpr (PASS == 2) cov_operand_store(a.wop_fp32, a.wop_hl, a.q, nch, ch, b, t, l16, l4, d[t]);
         }
-        if constexpr (PASS == 2 && NT == 1) {  // the FP32 block's other 16 columns
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            a.wop_fp32[(int64_t)ch * 2048 + (4 * (b & 1) + i) * 256 + (32 * (b >> 1) + 16 + l16) * 4 + l4] = 0.0f;
-        }
+        if constexpr (PASS == 2 && NT == 1)  // the FP32 block's other 16 columns
+          cov_operand_store(a.wop_fp32, a.wop_hl, a.q, nch, ch, b, 1, l16, l4, f64x4{0.0, 0.0, 0.0, 0.0});
       }
       if constexpr (PASS < 2) {  // a product's accumulator layout is both operands' layout
 #pragma unroll
@@ -442,7 +454,7 @@ __global__ __launch_bounds__(1024) void gram_factor_kernel(GramArgs a) {
   for (int t = 0; t < (q <= 16 ? 1 : kGramTiles); ++t) {
     const int r = tid >> 8, e = tid & 255;
     double v = 0.0;
-#pragma unroll 8
+#pragma unroll 32
     for (int w = a.waves * r / 4; w < a.waves * (r + 1) / 4; ++w) v += a.part[((int64_t)w * kGramTiles + t) * 256 + e];
     sum[r][e] = v;
     __syncthreads();
@@ -3031,6 +3043,11 @@ static int gram_waves(int64_t n_pad) {  // about four chunks a wave, at most 256
 hipError_t launch_gram_qr(const double* C, int64_t ldc, int64_t n, int64_t n_pad, int q, double* Q1, double* Q,
                           double* scratch, int32_t* flags, void* wop_fp32, void* const* wop_hl, hipStream_t s) {
   if (q < 1 || q > kSlots) return hipErrorInvalidValue;
+  if (q == 1) {
+    hipLaunchKernelGGL(intercept_kernel, dim3((unsigned)std::min<int64_t>(1024, n_pad / kChunk)), dim3(256), 0, s, Q, n,
+                       n_pad);
+    return launch_cov_operands(Q, n, n_pad, q, wop_fp32, wop_hl, s);
+  }
   GramArgs a{};
   a.C = C;
   a.ldc = ldc;
@@ -3069,8 +3086,8 @@ hipError_t launch_gram_qr(const double* C, int64_t ldc, int64_t n, int64_t n_pad
 hipError_t launch_cov_operands(const double* Q, int64_t n, int64_t n_pad, int q, void* wop_fp32,
                                void* const* wop_hl, hipStream_t s) {
   if (!wop_fp32 || !wop_hl[kSplit] || !wop_hl[kSplit16]) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(cov_operand_kernel, dim3(256), dim3(256), 0, s, Q, n, n_pad, q, wop_fp32, wop_hl[kSplit],
-                     wop_hl[kSplit16]);
+  CovOperandArgs a{Q, n_pad, q, (float*)wop_fp32, {(char*)wop_hl[kSplit], (char*)wop_hl[kSplit16]}};
+  hipLaunchKernelGGL(cov_operand_kernel, dim3((unsigned)(n_pad / kChunk)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

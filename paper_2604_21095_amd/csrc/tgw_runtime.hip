@@ -343,8 +343,7 @@ extern "C" tgw_status tgw_fit_covariates(int64_t n_samples, int32_t n_cov, const
     e = launch_gram_qr(d_C, ldc, n_samples, cov->n_pad, cov->q, X, cov->Q, qrs, flags, cov->wop_fp32, cov->wop_hl, s);
   read_flags();
   if (e == hipSuccess && !hf[0] && hf[2]) {  // ill-conditioned: the Householder QR, which also decides on the rank
-    e = hipMemsetAsync(flags, 0, sizeof(hf), s);
-    if (e == hipSuccess) e = launch_qr(d_C, ldc, n_samples, cov->n_pad, cov->q, X, cov->Q, rdiag, qrs, flags, s);
+    e = launch_qr(d_C, ldc, n_samples, cov->n_pad, cov->q, X, cov->Q, rdiag, qrs, flags, s);
     if (e == hipSuccess)
       e = launch_cov_operands(cov->Q, n_samples, cov->n_pad, cov->q, cov->wop_fp32, cov->wop_hl, s);
     read_flags();
