@@ -772,15 +772,20 @@ static hipError_t launch_tiles(const void* fn, const GemmArgs& a, int64_t tiles,
   return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(256), params, 0, s);
 }
 
+// workgroups per launch: a grid holds less than 2^32 threads
+constexpr int64_t kMaxGroups = int64_t(1) << 23;
+
 hipError_t launch_gemm_small(int idx, int prec, int mode, int nqb, const GemmArgs& a, hipStream_t s, bool g8) {
-  const int64_t tiles = (int64_t)a.n_mtiles * a.n_ctiles;
-  if (prec == kFP32) return launch_tiles(gemm_small_fp32_fn(idx, mode, g8), a, tiles, s);
-  if (a.n_segs <= 1) return launch_tiles(small_kernel<0>(idx, prec, mode, nqb, g8), a, tiles, s);
-  // as many tiles at a time as a.part holds the segments of: whole rows of
-  // column tiles where one row fits, else parts of a row
+  if (prec == kFP32)  // these walk their tiles
+    return launch_tiles(gemm_small_fp32_fn(idx, mode, g8), a,
+                        std::min((int64_t)a.n_mtiles * a.n_ctiles, kMaxGroups), s);
+  // as many tiles at a time as a launch takes and a.part holds the segments of:
+  // whole rows of column tiles where one row fits, else parts of a row
   const TileShape t = kSmall[idx];
-  const int64_t fit = a.part_bytes / ((int64_t)t.waves * t.wm_frags * (mode == kRawHL ? 1 : t.wn_frags + nqb) * 4096 *
-                                      a.n_segs);
+  int64_t fit = kMaxGroups;
+  if (a.n_segs > 1)
+    fit = std::min(fit / a.n_segs, a.part_bytes / ((int64_t)t.waves * t.wm_frags *
+                                                   (mode == kRawHL ? 1 : t.wn_frags + nqb) * 4096 * a.n_segs));
   if (fit < 1) return hipErrorInvalidValue;
   const int nc = (int)std::min<int64_t>(a.n_ctiles, fit);
   const int64_t nm = fit / nc;
@@ -793,6 +798,10 @@ hipError_t launch_gemm_small(int idx, int prec, int mode, int nqb, const GemmArg
       b.n_mtiles = (int)std::min<int64_t>(nm, a.n_mtiles - m0);
       b.n_ctiles = std::min(nc, a.n_ctiles - c0);
       const int64_t n = (int64_t)b.n_mtiles * b.n_ctiles;
+      if (a.n_segs <= 1) {
+        e = launch_tiles(small_kernel<0>(idx, prec, mode, nqb, g8), b, n, s);
+        continue;
+      }
       e = launch_tiles(small_kernel<1>(idx, prec, mode, nqb, g8), b, n, s, n * (a.n_segs - 1));
       if (e == hipSuccess) e = launch_tiles(small_kernel<2>(idx, prec, mode, nqb, g8), b, n, s);
     }
