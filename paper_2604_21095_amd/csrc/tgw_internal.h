@@ -281,7 +281,7 @@ hipError_t launch_prep(const void* Y, int y_fp64, int64_t ldy, int64_t n, int64_
                        const double* Q, int q, int prec, void* yop, float* scale, float* invny, float* cw,
                        uint8_t* lscale, int32_t* flags, void* scratch, hipStream_t s);
 // bytes of launch_prep's scratch (0: none); without it (NULL) one workgroup prepares two columns
-size_t prep_scratch_bytes(int64_t n_pad, int64_t P);
+size_t prep_scratch_bytes(int64_t n_pad, int64_t P, int q);
 hipError_t launch_set_operand(const float* V, int64_t ldv, int64_t n, int64_t n_pad, int64_t P, int prec,
                               void* yop, uint8_t* lscale, hipStream_t s);
 hipError_t launch_table(float4* table, double df, hipStream_t s);

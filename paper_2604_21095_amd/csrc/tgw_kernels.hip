@@ -761,6 +761,7 @@ struct PrepArgs {
   const double* Q;
   int q, y_fp64;
   int n_tiles, segs;      // 16-column tiles, sample segments
+  int slots;              // 16 per slot tile of the covariate basis (kPrepMore more follow)
   void* yop;
   double* part;           // [slots][segs][16 n_tiles]
   double* sums;           // [slots][16 n_tiles]: A's, then D's in the second half
@@ -772,10 +773,12 @@ struct PrepArgs {
   float* cw;
   int32_t* flags;
 };
-constexpr int kPrepSlotV = kSlots;        // sum of v (D: sum of the operand)
-constexpr int kPrepSlotVV = kSlots + 1;   // sum of v^2 (D: its square)
-constexpr int kPrepSlotL = kSlots + 2;    // D: sum of the lo terms
-constexpr int kPrepSlots = kSlots + 3;
+// slots of the sums after those of Q^T v
+constexpr int kPrepV = 0;   // sum of v (D: sum of the operand)
+constexpr int kPrepVV = 1;  // sum of v^2 (D: its square)
+constexpr int kPrepL = 2;   // D: sum of the lo terms
+constexpr int kPrepMore = 3;
+__host__ __device__ constexpr int prep_slot_tiles(int q) { return q <= 16 ? 1 : 2; }
 
 // y at samples s0 + 4 i (s0 = first + l4) of this lane's column; zero past n
 template <bool F64>
@@ -884,8 +887,8 @@ __global__ __launch_bounds__(256, 4) void prep_project_kernel(PrepArgs a) {
   sv = prep_col_sum(sv);
   svv = prep_col_sum(svv);
   if (w.l4 == 0) {
-    a.part[prep_at(a, kPrepSlotV, w.seg, c)] = sv;
-    a.part[prep_at(a, kPrepSlotVV, w.seg, c)] = svv;
+    a.part[prep_at(a, 16 * NT + kPrepV, w.seg, c)] = sv;
+    a.part[prep_at(a, 16 * NT + kPrepVV, w.seg, c)] = svv;
   }
 }
 
@@ -935,10 +938,10 @@ __device__ __forceinline__ double prep_qty(const PrepArgs& a, int k, int64_t c, 
 __device__ __forceinline__ PrepColumn prep_column(const PrepArgs& a, int64_t c, double y0, double* delta) {
   const int64_t nc = 16 * (int64_t)a.n_tiles;
   PrepColumn p;
-  const double d = a.sums[kPrepSlotV * nc + c] / (double)a.n;
+  const double d = a.sums[(a.slots + kPrepV) * nc + c] / (double)a.n;
   p.mean = y0 + d;
   *delta = d;
-  const double v2 = a.sums[kPrepSlotVV * nc + c];
+  const double v2 = a.sums[(a.slots + kPrepVV) * nc + c];
   p.yc2 = fmax(v2 - (double)a.n * d * d, 0.0);
   double s = p.yc2;
 #pragma unroll 8
@@ -1098,9 +1101,9 @@ __global__ __launch_bounds__(256, PASS == 2 ? 3 : 4) void prep_residual_kernel(P
     s2 = prep_col_sum(s2);
     sl = prep_col_sum(sl);
     if (w.l4 == 0) {
-      a.part[prep_at(a, kPrepSlotV, w.seg, c)] = s1;
-      a.part[prep_at(a, kPrepSlotVV, w.seg, c)] = s2;
-      a.part[prep_at(a, kPrepSlotL, w.seg, c)] = sl;
+      a.part[prep_at(a, 16 * NT + kPrepV, w.seg, c)] = s1;
+      a.part[prep_at(a, 16 * NT + kPrepVV, w.seg, c)] = s2;
+      a.part[prep_at(a, 16 * NT + kPrepL, w.seg, c)] = sl;
     }
   }
 }
@@ -1116,21 +1119,21 @@ __global__ __launch_bounds__(256) void prep_finish_kernel(PrepArgs a, int prec) 
   const PrepColumn pc = prep_column(a, p, a.y_fp64 ? *(const double*)colp : (double)*(const float*)colp, &delta);
   const double sp = sqrt(pc.direct ? pc.r2 : a.r2[p]);
   const bool valid = sp > 1e-12 * sqrt(pc.yc2);
-  const double* d = a.sums + kPrepSlots * nc + p;  // pass D's
+  const double* d = a.sums + (a.slots + kPrepMore) * nc + p;  // pass D's
   if (lane == 0) {
     double proj = 0.0;
     for (int k = 0; k < a.q; ++k) proj += d[k * nc] * d[k * nc];
-    const double ny2 = d[kPrepSlotVV * nc] - proj;
+    const double ny2 = d[(a.slots + kPrepVV) * nc] - proj;
     a.scale[p] = (float)sp;
     a.invny[p] = (valid && ny2 > 0.0) ? (float)(1.0 / sqrt(ny2)) : __builtin_nanf("");
     if (prec == kSplit8) a.lscale[p] = (uint8_t)(127 - lo_shift(a.maxlo[p]));
   }
   if (lane < kSlots) {
     float v = 0.0f;
-    if (lane == 0) v = (float)(-d[kPrepSlotV * nc]);
+    if (lane == 0) v = (float)(-d[(a.slots + kPrepV) * nc]);
     if (lane >= 1 && lane < a.q) v = (float)(-d[lane * nc]);
     // FP16 + FP8 form with q <= 31: the last slot takes minus the column's sum of lo terms (see prep_kernel)
-    if (lane == kLoSlot && prec == kSplit8 && a.q <= kLoSlot) v = (float)(-d[kPrepSlotL * nc]);
+    if (lane == kLoSlot && prec == kSplit8 && a.q <= kLoSlot) v = (float)(-d[(a.slots + kPrepL) * nc]);
     a.cw[p * kSlots + lane] = v;
   }
 }
@@ -3100,10 +3103,10 @@ static int prep_segments(int64_t n_pad, int64_t P) {
 // launches (about 40 us) cost more than prep_kernel's one (38 us at N = 2,000)
 constexpr int64_t kPrepSplitMin = 64 * kChunk;
 
-size_t prep_scratch_bytes(int64_t n_pad, int64_t P) {
+size_t prep_scratch_bytes(int64_t n_pad, int64_t P, int q) {
   if (n_pad < kPrepSplitMin) return 0;
   const int64_t nc = (P + 15) / 16 * 16;
-  return sizeof(double) * (size_t)(nc * ((int64_t)kPrepSlots * (prep_segments(n_pad, P) + 2) + 2));
+  return sizeof(double) * (size_t)(nc * ((16 * (int64_t)prep_slot_tiles(q) + kPrepMore) * (prep_segments(n_pad, P) + 2) + 2));
 }
 
 template <int PREC, int NT, bool F64>
@@ -3112,7 +3115,7 @@ static void launch_prep_passes(const PrepArgs& a, unsigned grid, hipStream_t s) 
   const int64_t nc = 16 * (int64_t)a.n_tiles;
   const double* part = a.part;
   hipLaunchKernelGGL((prep_project_kernel<NT, F64>), g, b, 0, s, a);
-  hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, kPrepSlots), b, 0, s, part, a.sums, a.segs, nc);
+  hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, a.slots + kPrepMore), b, 0, s, part, a.sums, a.segs, nc);
   hipLaunchKernelGGL((prep_residual_kernel<0, kFP32, NT, F64>), g, b, 0, s, a);
   hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, 1), b, 0, s, part, a.r2, a.segs, nc);
   if (PREC == kSplit8) {
@@ -3120,7 +3123,7 @@ static void launch_prep_passes(const PrepArgs& a, unsigned grid, hipStream_t s) 
     hipLaunchKernelGGL(prep_sum_kernel<true>, dim3(a.n_tiles, 1), b, 0, s, part, a.maxlo, a.segs, nc);
   }
   hipLaunchKernelGGL((prep_residual_kernel<2, PREC, NT, F64>), g, b, 0, s, a);
-  hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, kPrepSlots), b, 0, s, part, a.sums + kPrepSlots * nc,
+  hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, a.slots + kPrepMore), b, 0, s, part, a.sums + (a.slots + kPrepMore) * nc,
                      a.segs, nc);
   hipLaunchKernelGGL(prep_finish_kernel, dim3((unsigned)((a.P + 3) / 4)), b, 0, s, a, PREC);
 }
@@ -3143,7 +3146,8 @@ hipError_t launch_prep(const void* Y, int y_fp64, int64_t ldy, int64_t n, int64_
     a.yop = yop;
     const int64_t nc = 16 * (int64_t)a.n_tiles;
     a.sums = (double*)scratch;
-    a.r2 = a.sums + 2 * kPrepSlots * nc;
+    a.slots = 16 * prep_slot_tiles(q);
+    a.r2 = a.sums + 2 * (a.slots + kPrepMore) * nc;
     a.maxlo = a.r2 + nc;
     a.part = a.maxlo + nc;
     a.lscale = lscale;
@@ -3154,7 +3158,7 @@ hipError_t launch_prep(const void* Y, int y_fp64, int64_t ldy, int64_t n, int64_
     const unsigned grid = (unsigned)(((int64_t)a.n_tiles * a.segs + 3) / 4);
     auto go = [&](auto p) {
       constexpr int PREC = decltype(p)::value;
-      if (q <= 16)
+      if (prep_slot_tiles(q) == 1)
         y_fp64 ? launch_prep_passes<PREC, 1, true>(a, grid, s) : launch_prep_passes<PREC, 1, false>(a, grid, s);
       else
         y_fp64 ? launch_prep_passes<PREC, 2, true>(a, grid, s) : launch_prep_passes<PREC, 2, false>(a, grid, s);

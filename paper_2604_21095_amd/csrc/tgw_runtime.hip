@@ -439,7 +439,7 @@ extern "C" tgw_status tgw_prepare_phenotypes(const tgw_covariates* cov, int64_t 
   if (e == hipSuccess) e = hipMemsetAsync(flags, 0, sizeof(int32_t), s);
   // where there is no room for the scratch, the preparation that needs none runs
   void* work = nullptr;
-  const size_t work_bytes = prep_scratch_bytes(cov->n_pad, n_pheno);
+  const size_t work_bytes = prep_scratch_bytes(cov->n_pad, n_pheno, cov->q);
   if (e == hipSuccess && work_bytes && dev_alloc(A, &work, work_bytes, s) != hipSuccess) {
     work = nullptr;
     (void)hipGetLastError();
