@@ -12,7 +12,7 @@
  *   - genotypes are then streamed in marker blocks, each block contracted
  *     with the prepared panel (Eq. 2) and turned into t-statistics (Eq. 3)
  *     and p-values                                -> tgw_scan
- *   - Q comes from a Householder QR of [1 | C]    -> tgw_fit_covariates
+ *   - Q comes from a QR of [1 | C]                -> tgw_fit_covariates
  * Readings of points the paper leaves open (used throughout):
  *   - genotypes are covariate-adjusted as well (exact Frisch-Waugh-Lovell
  *     partial correlation); at K = 0 this is exactly the paper's Eq. 2-3;
@@ -90,8 +90,8 @@ typedef enum {
  *                       FP16 pass plus one FP8 pass at twice the FP16 rate.
  * In every form a marker without missing calls takes gs = 1 and the integer
  * c = rint(mu) instead (no missing value to carry).
- *                       Runs on the wide tile shapes only (tiles 1 and 6
- *                       select their own; every other index selects tile 0).
+ *                       Of the named tile shapes it has the wide ones (tiles 1
+ *                       and 6; every other index selects tile 0).
  * Covariate QR, phenotype norms and the extreme-tail p-values stay FP64. */
 typedef enum {
   TGW_PREC_FP32 = 0,
@@ -273,13 +273,16 @@ int32_t tgw_abi_version(void);
 tgw_status tgw_init(void);
 
 /* ---- covariates (paper Methods 2.2, Eq. 1: Q spans the covariate space) --
- * Builds Q (n_samples x q, q = n_cov + 1, orthonormal columns) by an FP64
- * Householder QR of X0 = [1 | C] on the GPU.  The intercept is always added.
+ * Builds Q (n_samples x q, q = n_cov + 1, orthonormal columns) by an FP64 QR
+ * of X0 = [1 | C] on the GPU, with the column signs of Householder reflections
+ * (R_jj = -sign(pivot) |R_jj|): Cholesky twice, or the reflections themselves
+ * where the columns are ill-conditioned.  The intercept is always added.
  * The reductions run over a fixed grid in a fixed order, so the same C gives
  * the same Q bit for bit in every call.
  *   d_C   device FP64, column-major n_samples x n_cov, leading dim ldc >= n_samples
  *         (may be NULL when n_cov == 0).  Not retained.
- * Synchronizes `stream` once to report:
+ * Synchronizes `stream` once (twice where the columns are ill-conditioned) to
+ * report:
  *   TGW_ERR_NONFINITE if C holds NaN/Inf; TGW_ERR_RANK_DEFICIENT if
  *   |R_jj| <= 1e-10 max_i |R_ii|; TGW_ERR_SHAPE unless n_samples >= n_cov + 3
  *   and 0 <= n_cov <= 31. */
@@ -298,6 +301,11 @@ tgw_status tgw_covariates_q(const tgw_covariates* cov, double* d_Q, int64_t ldq,
  *   d_Y   device, column-major n_samples x n_pheno, FP32 (y_is_fp64 = 0) or
  *         FP64 (y_is_fp64 = 1), leading dim ldy >= n_samples.  Not retained.
  * The panel keeps a reference to `cov`; free panels before their covariates.
+ * From 4,096 samples on the sums run over sample segments whose partial sums
+ * take a temporary buffer (20 MB, with more than 15 covariates 37 MB, more from
+ * 131,072 phenotypes on).  Where the allocator has no room for it the panel is
+ * prepared without, with sums in another order: the last bits of the panel, and
+ * so of the scan, can then differ.
  * Synchronizes `stream` once; TGW_ERR_NONFINITE on NaN/Inf in Y. */
 tgw_status tgw_prepare_phenotypes(const tgw_covariates* cov, int64_t n_pheno, const void* d_Y,
                                   int32_t y_is_fp64, int64_t ldy, tgw_precision prec,
@@ -310,7 +318,9 @@ tgw_status tgw_panel_info(const tgw_panel* panel, int64_t* n, int64_t* p, int32_
  * Groups one or more prepared panels that share n_samples and precision
  * (the batching form: uneven P and K run through one persistent launch over
  * the virtual concatenation of all their columns) and allocates the scan
- * workspace.  `panels` must stay alive while the plan is used. */
+ * workspace (with the FP16 forms and more than 65,536 samples up to 64 MiB for
+ * the sums of sample segments, less where the allocator has less).  `panels`
+ * must stay alive while the plan is used. */
 tgw_status tgw_plan_create(const tgw_panel* const* panels, int32_t n_panels,
                            const tgw_plan_options* opts, tgw_plan** out);
 void tgw_plan_free(tgw_plan* plan);
@@ -324,7 +334,9 @@ tgw_status tgw_tile_shape(int32_t idx, int32_t* tile_markers, int32_t* tile_cols
  * (one block at most) with HIP events, keeps the fastest for this plan and
  * records it in a JSON cache keyed by (arch, padded samples, column blocks,
  * panels, precision): $TGW_TUNE_CACHE, default ~/.cache/tgw/tune.json.  A
- * later plan with the same key takes the cached shape without timing.
+ * later plan with the same key takes the cached shape without timing.  A plan
+ * that names no tile may still take smaller tiles for a block, by their cost
+ * against the shape that was found.
  * Writes scratch results into `outs` (it scans the markers several times, so
  * zero best and topk again before the real scan); synchronizes `stream`.
  * best_ms may be NULL. */
@@ -348,8 +360,8 @@ tgw_status tgw_plan_autotune(tgw_plan* plan, const uint8_t* d_geno, int64_t n_ma
  * (error <= about 2^-18 in BF16, 2^-21 in FP16); the intercept of the
  * covariate projection removes c exactly and the epilogue divides by gs.  8-bit dosages enter as q - c with the integer c = round(mu) in
  * units of 1/127 (exact in FP16 and FP32), a missing one as mu - c (error <=
- * 2^-12 / 127 in FP16).  They run the register-staged tile shapes; the
- * autotuner keeps a separate choice for them.
+ * 2^-12 / 127 in FP16).  The autotuner keeps a separate choice of tile for
+ * them (default: the register-staged shape 2; FP16 + FP8: tile 0).
  * Results are deterministic run to run.  A scan split into several marker
  * ranges gives bitwise the same outputs as one call when every boundary is a
  * multiple of 512 markers from m_begin (any boundary for FP32 and the 16-bit

@@ -269,7 +269,8 @@ __device__ __forceinline__ void cov_operand_store(float* wop_fp32, char* const (
   // first half; the second half is never read), dword l4 of step j = 2 (b & 1)
   // + (i & 1) holding samples i and i + 2
   if (t < hl_blocks(n_slots)) {
-    const int64_t at = ((int64_t)t * n_chunks + ch) * kBlockBytes + 2 * (b & 1) * 1024 + (b >> 1) * 512 + l16 * 16 + 4 * l4;
+    const int64_t at =
+        ((int64_t)t * n_chunks + ch) * kBlockBytes + 2 * (b & 1) * 1024 + (b >> 1) * 512 + l16 * 16 + 4 * l4;
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
       uint32_t hb[4], lb[4];
@@ -324,6 +325,7 @@ __global__ __launch_bounds__(256) void intercept_kernel(double* Q, int64_t n, in
 // Gram matrix of X = [1 | C] with unit columns gives R and Q1 = X R^-1, whose
 // own Gram matrix, the unit matrix to cond(X)^2 rounding errors, corrects it
 // to Q orthonormal to rounding.  Five launches instead of six per column.
+// (The intercept alone needs no factorization: intercept_kernel.)
 // Taken when every pivot of the first factorization is above kGramPivot
 // (condition below about 1e4: Q is then as accurate as the Householder QR's);
 // otherwise flags[2] is set, the caller runs the Householder QR above, and
@@ -735,7 +737,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const void* __restri
 
 // ---------------------------------------------------------------------------
 // phenotype preparation over sample segments (cohorts of kPrepSplitMin
-// chunks and more): the same quantities as prep_kernel, with the projections
+// samples and more): the same quantities as prep_kernel, with the projections
 // on the FP64 matrix cores and the samples of 16 columns cut into S segments,
 // one wave each, so that a panel of any width fills the GPU and each element
 // of Q read serves 16 columns.  Each pass leaves its sums per segment
@@ -3099,14 +3101,16 @@ static int prep_segments(int64_t n_pad, int64_t P) {
   const int64_t tiles = (P + 15) / 16;
   return (int)std::max<int64_t>(1, std::min<int64_t>((8192 + tiles - 1) / tiles, n_pad / kChunk / 2));
 }
-// cohorts from here on take the split preparation: below, its nine short
-// launches (about 40 us) cost more than prep_kernel's one (38 us at N = 2,000)
+// cohorts from here on take the split preparation: below, its seven short
+// launches (nine in the FP16 + FP8 form, about 40 us) cost more than
+// prep_kernel's one (38 us at N = 2,000)
 constexpr int64_t kPrepSplitMin = 64 * kChunk;
 
 size_t prep_scratch_bytes(int64_t n_pad, int64_t P, int q) {
   if (n_pad < kPrepSplitMin) return 0;
   const int64_t nc = (P + 15) / 16 * 16;
-  return sizeof(double) * (size_t)(nc * ((16 * (int64_t)prep_slot_tiles(q) + kPrepMore) * (prep_segments(n_pad, P) + 2) + 2));
+  const int64_t sums = 16 * prep_slot_tiles(q) + kPrepMore;  // per column and segment, and twice per column
+  return sizeof(double) * (size_t)(nc * (sums * (prep_segments(n_pad, P) + 2) + 2));
 }
 
 template <int PREC, int NT, bool F64>
@@ -3123,8 +3127,8 @@ static void launch_prep_passes(const PrepArgs& a, unsigned grid, hipStream_t s) 
     hipLaunchKernelGGL(prep_sum_kernel<true>, dim3(a.n_tiles, 1), b, 0, s, part, a.maxlo, a.segs, nc);
   }
   hipLaunchKernelGGL((prep_residual_kernel<2, PREC, NT, F64>), g, b, 0, s, a);
-  hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, a.slots + kPrepMore), b, 0, s, part, a.sums + (a.slots + kPrepMore) * nc,
-                     a.segs, nc);
+  hipLaunchKernelGGL(prep_sum_kernel<false>, dim3(a.n_tiles, a.slots + kPrepMore), b, 0, s, part,
+                     a.sums + (a.slots + kPrepMore) * nc, a.segs, nc);
   hipLaunchKernelGGL(prep_finish_kernel, dim3((unsigned)((a.P + 3) / 4)), b, 0, s, a, PREC);
 }
 

@@ -889,7 +889,7 @@ static hipError_t enqueue_redo(tgw_plan* pl, const ScanCall& c, int64_t m0, hipS
   r.outs = pl->d_outs;
   r.hits = pl->hits;
   r.redo = RedoDev{pl->redo_entries, pl->redo_count, pl->MB};
-  return launch_redo(r, pl->n_cu, s);  // one workgroup fits on a CU (137 KiB of LDS)
+  return launch_redo(r, pl->n_cu, s);  // one workgroup fits on a CU (134 KiB of LDS)
 }
 
 static hipError_t enqueue_main(tgw_plan* pl, const ScanCall& c, int64_t m0, int64_t nm, int tile, const MainPath& mp,

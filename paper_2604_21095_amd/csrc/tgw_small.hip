@@ -655,7 +655,8 @@ double insert_us(const ScanShape& s, int i) {
   double gain = m <= 1500 ? 60.0 : 25.0;
   if (s.n_cb == 3) gain *= 0.6;
   if (half) gain = m > 1500 ? 15.0 : p < 8000 ? 25.0 : 0.0;
-  const double rounds = p >= 4000 && s.n_chunks < 64 ? 12.0 * (ceil_div(n_tiles(s.nm, s.n_cb, kWide), s.n_cu) - 1) : 0.0;
+  const double rounds =
+      p >= 4000 && s.n_chunks < 64 ? 12.0 * (ceil_div(n_tiles(s.nm, s.n_cb, kWide), s.n_cu) - 1) : 0.0;
   if (i == 1) return rounds - gain;
   if (i == 0)
     return rounds - gain + (p >= 3000 ? 2e-3 * p : m >= 1000 && s.n_chunks < 32 ? 6.0 : 0.0) - (m < 1000 ? 8.0 : 0.0);

@@ -536,8 +536,8 @@ class Plan:
         return shift, mean, scale
 
     def debug_path(self, n_markers: int, code=CODE_DOSAGE, topk: int = 0) -> int:
-        """What tests a block of n_markers markers (filling top-k lists of topk entries): 0 the plan's tile, 1 + i small tile i, 17 + i the
-        same with Q^T g beside the tests."""
+        """What tests a block of n_markers markers (filling top-k lists of topk entries): 0 the plan's
+        tile, 1 + i small tile i, 17 + i the same with Q^T g beside the tests."""
         p = _i32()
         _check(_dbg_path(self._h, code, n_markers, topk, ctypes.byref(p)), "tgw_debug_path")
         return p.value
