@@ -4,6 +4,7 @@
 #include "tgw_device.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace tgw {
 
@@ -633,11 +634,32 @@ double small_cycles(const ScanShape& s, int i) {
 // markers, k = 50, N = 500: 1.0 ms on wide tiles, 1.6 on 256 x 32, 2.2 on 128 x
 // 32), most of all in one burst, where the contraction is short.  The
 // register-staged default tiles of FP32 and of 8-bit dosages in the FP16 split
-// have half the rows per wave.  With these terms, of 2,225 scans three are more
-// than 5 % and eleven more than 2 % slower than on the wide tile (14 % at the
-// most); without them up to 2.2 times.
+// have half the rows per wave.
+// Above two column blocks the terms are a least-squares fit to 2,620 scans
+// (N = 500 to 60,000, 500 to 60,000 markers, 65 to 20,480 phenotypes, k = 1,
+// 10, 50), kept within the range that they were fitted to.  The shape they
+// give takes 1.3 % longer than the fastest one on average (25 % at the most),
+// and four of the scans are more than 5 % slower than on the wide tile (14 % at
+// the most).  Without any term for the lists it is 7.6 % (94 %), and up to 1.55
+// times the wide tile's time.
+struct InsertFit {
+  double one, m, mm, n, rounds, p, pn, p4;
+};
+const InsertFit* insert_fit(bool fp32) {
+  static const InsertFit f16[kNumSmall] = {{-45, 21.2, -4.9, -1.1, -5.4, 15.9, -1.07, 10.5},
+                                           {-43, 18.7, -3.7, -0.5, -6, 9.6, -1.37, 4.6},
+                                           {-33, 22.3, -4.5, -0.7, -7.1, 16.9, -1.08, 4.1},
+                                           {-34, 17.5, -2.7, -0.6, -5.7, 8.4, -0.57, 0.1},
+                                           {-24, 23, -1.5, -0.9, -8.5, 14, -0.61, -0.3}};
+  static const InsertFit f32[kNumSmall] = {{-27, 9.2, -3.8, 1.9, -4.4, 9.2, -1.87, 9.8},
+                                           {-23, 6.4, -2.8, 2.8, -6.3, 5, -2.08, -0.5},
+                                           {-17, 10.7, -3.5, 3.3, -5, 13.6, -1.28, 3},
+                                           {-17, 4.9, -2.6, 2.5, -2.4, 6.2, -0.72, -2},
+                                           {-10, 10.2, -0.8, 2.4, -4.6, 11.1, -0.19, -0.3}};
+  return fp32 ? f32 : f16;
+}
 double insert_us(const ScanShape& s, int i) {
-  const double m = (double)s.nm, p = 32.0 * s.n_cb;
+  const double m = (double)s.nm;
   const bool half = s.prec == kFP32 || (s.prec == kSplit16 && s.g8);
   if (s.n_cb <= 2) {
     double narrow;  // 256 x 32
@@ -652,18 +674,13 @@ double insert_us(const ScanShape& s, int i) {
     if (s.n_cb == 1) return narrow + std::min(5e-4 * m, 20.0) - 1.5;
     return s.prec == kFP32 ? narrow : narrow + std::min(4e-4 * m, 16.0) - 4.0;
   }
-  double gain = m <= 1500 ? 60.0 : 25.0;
-  if (s.n_cb == 3) gain *= 0.6;
-  if (half) gain = m > 1500 ? 15.0 : p < 8000 ? 25.0 : 0.0;
-  const double rounds =
-      p >= 4000 && s.n_chunks < 64 ? 12.0 * (ceil_div(n_tiles(s.nm, s.n_cb, kWide), s.n_cu) - 1) : 0.0;
-  if (i == 1) return rounds - gain;
-  if (i == 0)
-    return rounds - gain + (p >= 3000 ? 2e-3 * p : m >= 1000 && s.n_chunks < 32 ? 6.0 : 0.0) - (m < 1000 ? 8.0 : 0.0);
-  double t = rounds - 0.6 * gain;  // 256 x 64
-  if (i != 3) t += (s.n_chunks < 128 ? 5e-3 : 2e-3) * std::max(0.0, p - 4000.0);
-  if (i == 4 && m > 8000) t += 10.0;
-  return t;
+  const InsertFit& f = insert_fit(s.prec == kFP32)[i];
+  const double lm = std::log(std::clamp(m, 500.0, 40000.0) / 3000.0);
+  const double ln = std::log(std::clamp((double)s.n_chunks, 8.0, 1000.0) / 64.0);
+  const double p = std::min(32.0 * s.n_cb, 20480.0) / 4000.0;
+  const double rounds = (double)std::min<int64_t>(ceil_div(n_tiles(s.nm, s.n_cb, kWide), s.n_cu), 12);
+  return f.one + f.m * lm + f.mm * lm * lm + f.n * ln + f.rounds * rounds + f.p * p + f.pn * p * ln +
+         f.p4 * std::min(p, 1.0);
 }
 }  // namespace
 

@@ -73,3 +73,35 @@ def test_uneven_segments(tgw, precision, code, n, m, p):
 ])
 def test_outputs_and_lengths(tgw, precision, code, n, m, p, topk):
     assert _ratio(tgw, precision, code, n, m, p, topk) < 1.15
+
+
+@pytest.mark.parametrize("precision,code,n,m,p,topk", [
+    ("split16", "dosage", 1000, 8000, 7000, 50),
+    ("split8", "dosage8", 2000, 40_000, 4600, 50),
+    ("fp32", "dosage", 1000, 1500, 8000, 10),
+    ("fp32", "dosage8", 2000, 600, 16_000, 10),
+])
+def test_lists_take_a_fast_shape(tgw, precision, code, n, m, p, topk):
+    """Of the default tile and the five small ones, the automatic choice is the
+    fastest or near it (20 %)."""
+    g = torch.Generator(device="cuda").manual_seed(n + m + p)
+    row = (n + 63) // 64 * (64 if code == "dosage8" else 16)
+    c = tgw.CODE_DOSAGE8 if code == "dosage8" else tgw.CODE_DOSAGE
+    geno = torch.randint(0, 256, (m, row), generator=g, device="cuda", dtype=torch.uint8)
+    cov = tgw.fit_covariates(torch.randn((10, n), generator=g, device="cuda", dtype=torch.float64).t())
+    plan = tgw.Plan([tgw.prepare_phenotypes(cov, torch.randn((p, n), generator=g, device="cuda").t(), precision)])
+    words = tgw.make_topk([p], topk)[0]
+    choice = plan.debug_path(m, c, topk)
+    times = {}
+    for path in [*range(6)] * 4:
+        plan.debug_set_path(path)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        words.zero_()
+        a.record()
+        plan.scan(geno, [{"topk": words}], code=c)
+        b.record()
+        b.synchronize()
+        times.setdefault(path, []).append(a.elapsed_time(b))
+    times = {path: min(t) for path, t in times.items()}
+    say(f"case: {precision} {code} n={n} m={m} p={p} topk={topk}: path {choice}, ms {times}")
+    assert times[choice] < 1.2 * min(times.values())
