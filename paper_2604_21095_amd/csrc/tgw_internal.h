@@ -337,9 +337,10 @@ struct ScanShape {
   bool g8;
   int64_t nm;
   int n_cb, n_chunks, n_segs, seg_len, n_cu;
-  int topk_k;       // entries of the longest top-k list asked for
-  int nqb;          // packed covariate blocks of a one-panel plan in a split form, else 0
-  double wide_rel;  // time of the plan's tile over the default tile's
+  int64_t part_bytes;  // room for the segments' sums
+  int topk_k;          // entries of the longest top-k list asked for
+  int nqb;             // packed covariate blocks of a one-panel plan in a split form, else 0
+  double wide_rel;     // time of the plan's tile over the default tile's
 };
 struct SmallChoice {
   int shape = -1;      // < 0: the plan's tile is the faster one

@@ -816,6 +816,7 @@ static MainPath main_path(const tgw_plan* pl, int code, int64_t nm, int topk_k) 
   s.n_segs = pl->n_segs;
   s.seg_len = pl->n_segs > 1 ? seg_chunks(pl->prec, pl->n_chunks) : pl->n_chunks;
   s.n_cu = pl->n_cu;
+  s.part_bytes = pl->part_bytes;
   s.topk_k = topk_k;
   s.nqb = pl->n_panels == 1 && pl->w_mode == kRawHL ? hl_blocks(pl->panels[0]->cov->q) : 0;
   s.wide_rel = pl->wide_rel[g8];

@@ -611,9 +611,9 @@ double wide_cycles(const ScanShape& s) {
   return s.wide_rel * (double)ceil_div(n_tiles(s.nm, s.n_cb, kWide), s.n_cu) *
          (1e3 * c.kfixed + s.n_chunks * c.chunk + (s.n_segs - 1) * kSegFlush);
 }
-double small_cycles(const ScanShape& s, int i) {
+// one launch (a pair of them above one segment) of `tiles`
+double launch_cycles(const ScanShape& s, int i, int64_t tiles) {
   const TileCost& c = tile_cost(s.prec, s.g8);
-  const int64_t tiles = n_tiles(s.nm, s.n_cb, kSmall[i]);
   const double one = 1e3 * c.alone[i].kfixed + std::min(s.seg_len, s.n_chunks) * c.alone[i].chunk;
   const int64_t wgs = tiles * s.n_segs;
   if (wgs <= s.n_cu) return one;
@@ -623,6 +623,22 @@ double small_cycles(const ScanShape& s, int i) {
     chunks = std::max((double)ceil_div(whole, s.n_cu) * s.seg_len, (double)tiles * s.n_chunks / s.n_cu);
   }
   return std::max(one, ceil_div(wgs, s.n_cu) * 1e3 * c.shared[i].kfixed + chunks * c.shared[i].chunk);
+}
+// Segmented scans take a launch for as many tiles as the buffer for the
+// segments' sums holds, as launch_gemm_small cuts them.  The last one can be a
+// few tiles that cost a whole round: FP16 + FP8, N = 80,000, 2,000 markers x
+// 4,300 phenotypes on 256 x 64 tiles are 512 + 32 tiles and take 3.43 ms, on
+// wide ones 2.82.
+double small_cycles(const ScanShape& s, int i) {
+  const TileShape& t = kSmall[i];
+  if (s.n_segs <= 1) return launch_cycles(s, i, n_tiles(s.nm, s.n_cb, t));
+  const int64_t nm = ceil_div(s.nm, t.tm()), nc = ceil_div(s.n_cb, t.wn_frags);
+  const int64_t fit = s.part_bytes / ((int64_t)t.waves * t.wm_frags * t.wn_frags * 4096 * s.n_segs);
+  const int64_t c = std::max<int64_t>(1, std::min(nc, fit)), m = std::max<int64_t>(1, fit / c);
+  double sum = (double)(nm / m) * (nc / c) * launch_cycles(s, i, std::min(m, nm) * c);
+  if (nm % m) sum += (double)(nc / c) * launch_cycles(s, i, nm % m * c);
+  if (nc % c) sum += (double)nm * launch_cycles(s, i, nc % c);  // then m is 1
+  return sum;
 }
 
 // Filling top-k lists: microseconds per list entry that a shape takes more (or
@@ -699,9 +715,11 @@ static int small_fused_shape(const ScanShape& s) {
   return r1 * (r1 > 1 ? 1450 : 1720) < r0 * (r0 > 1 ? 830 : 1000) ? 1 : 0;
 }
 
-// A small tile has to be 1 % faster by the estimate.  FP16 + FP8, N = 60,000,
+// A small tile has to be 1 % faster by the estimate (FP16 + FP8, N = 60,000,
 // 10,000 markers x 1,000 phenotypes: 2.28 ms on the 128 x 64 tiles, 2.00 on the
-// wide ones.
+// wide ones), 10 % above 65,536 samples, where the estimate is rougher: of 718
+// such scans nine are then more than 2 % slower than on wide tiles (9 % at the
+// most), twenty with 1 %.
 SmallChoice small_choice(const ScanShape& s) {
   const bool fusable = s.prec != kFP32 && s.nqb > 0 && s.n_cb <= 2;
   if (fusable && s.topk_k == 0) return SmallChoice{small_fused_shape(s), true};
@@ -723,7 +741,7 @@ SmallChoice small_choice(const ScanShape& s) {
     else
       offer(i, false, t + q);
   }
-  return least < 0.99 * wide ? best : SmallChoice{};
+  return least < (s.n_chunks > kSegMin ? 0.9 : 0.99) * wide ? best : SmallChoice{};
 }
 
 // 256-row tiles once they fill the GPU (100,000 markers, N = 23,000: 0.21 ms

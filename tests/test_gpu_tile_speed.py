@@ -59,6 +59,12 @@ def test_uneven_segments(tgw, precision, code, n, m, p):
     assert _ratio(tgw, precision, code, n, m, p, 0) < 1.15
 
 
+def test_segments_over_two_launches(tgw):
+    """On 256 x 64 tiles the buffer for the segments' sums holds 512 of the 544
+    tiles, and the rest would take a whole round of their own."""
+    assert _ratio(tgw, "split8", "dosage", 80_000, 2000, 4300, 0) < 1.15
+
+
 @pytest.mark.parametrize("precision,code,n,m,p,topk", [
     ("split8", "dosage", 500, 30_000, 1, 50),     # many waves at one list
     ("split", "dosage", 500, 30_000, 20, 10),
