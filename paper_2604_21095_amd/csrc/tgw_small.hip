@@ -717,9 +717,17 @@ static int small_fused_shape(const ScanShape& s) {
 
 // A small tile has to be 1 % faster by the estimate (FP16 + FP8, N = 60,000,
 // 10,000 markers x 1,000 phenotypes: 2.28 ms on the 128 x 64 tiles, 2.00 on the
-// wide ones), 10 % above 65,536 samples, where the estimate is rougher: of 718
+// wide ones).  10 % above 65,536 samples, where the estimate is rougher: of 718
 // such scans nine are then more than 2 % slower than on wide tiles (9 % at the
-// most), twenty with 1 %.
+// most), twenty with 1 %.  10 % also for top-k lists of long sums in FP16 +
+// FP8: half a round of its wide tiles runs at a higher clock than a full chip
+// of small ones (N = 48,190, 985 markers x 8,419 phenotypes, k = 1: 1.68 ms
+// against 1.85 to 2.00), and of 514 top-k scans three are then more than 5 %
+// slower than on wide tiles (10 % at the most), ten (19 %) with 1 %.  For the
+// other forms and for 8-bit dosages neither figure changes.
+static double small_margin(const ScanShape& s) {
+  return s.n_chunks > kSegMin || (s.topk_k > 0 && s.prec == kSplit8 && !s.g8 && s.n_chunks > 200) ? 0.9 : 0.99;
+}
 SmallChoice small_choice(const ScanShape& s) {
   const bool fusable = s.prec != kFP32 && s.nqb > 0 && s.n_cb <= 2;
   if (fusable && s.topk_k == 0) return SmallChoice{small_fused_shape(s), true};
@@ -741,7 +749,7 @@ SmallChoice small_choice(const ScanShape& s) {
     else
       offer(i, false, t + q);
   }
-  return least < (s.n_chunks > kSegMin ? 0.9 : 0.99) * wide ? best : SmallChoice{};
+  return least < small_margin(s) * wide ? best : SmallChoice{};
 }
 
 // 256-row tiles once they fill the GPU (100,000 markers, N = 23,000: 0.21 ms

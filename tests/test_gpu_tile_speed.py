@@ -71,6 +71,7 @@ def test_segments_over_two_launches(tgw):
     ("split16", "dosage", 500, 100_000, 40, 50),
     ("fp32", "dosage", 1000, 2000, 20_480, 10),   # short sums, long lists
     ("split8", "dosage", 8000, 500, 20_480, 10),
+    ("split8", "dosage", 48_190, 985, 8419, 1),   # half a round of wide tiles, long sums
     ("split16", "dosage8", 1500, 2000, 5000, 50),
     ("split16", "dosage8", 1000, 1301, 18_643, 10),
     ("split8", "dosage8", 500, 60_000, 300, 10),
