@@ -456,7 +456,7 @@ __global__ __launch_bounds__(1024) void gram_factor_kernel(GramArgs a) {
   for (int t = 0; t < (q <= 16 ? 1 : kGramTiles); ++t) {
     const int r = tid >> 8, e = tid & 255;
     double v = 0.0;
-#pragma unroll 32
+#pragma unroll 8
     for (int w = a.waves * r / 4; w < a.waves * (r + 1) / 4; ++w) v += a.part[((int64_t)w * kGramTiles + t) * 256 + e];
     sum[r][e] = v;
     __syncthreads();
