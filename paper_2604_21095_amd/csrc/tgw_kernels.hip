@@ -1526,8 +1526,13 @@ __device__ __forceinline__ f64x4 operand_block(const char* blk, int b, uint32_t 
   return y;
 }
 
-template <int PREC, bool G8>
+// FAR: a slot's column of Q can lie 4 GiB and more behind the first one.
+// Addresses of 64 bits cost registers that the kernel does not have (it spills
+// four to six more): 902 against 862 us for an analysis with one lead marker at
+// N = 34,613, 1,993 markers x 27 phenotypes.
+template <int PREC, bool G8, bool FAR>
 __global__ __launch_bounds__(kRedoThreads) void redo_kernel(RedoArgs a) {
+  using Offset = std::conditional_t<FAR, int64_t, uint32_t>;
   __shared__ double part[kRedoWaves][kRedoGroup * kRedoCols];  // the waves' sums: slots, then tests
   __shared__ double w_s[kSlots][kRedoGroup];
   __shared__ double h2_s[kRedoWaves][kRedoGroup];
@@ -1569,8 +1574,8 @@ __global__ __launch_bounds__(kRedoThreads) void redo_kernel(RedoArgs a) {
     {
       f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
       // step i contracts samples 16 b + 4 l4 + i: a lane reads 32 bytes of its slot's column at once
-      const int64_t o0 = (min(l16, q - 1) * a.n_pad + 4 * l4) * 8;
-      const int64_t o1 = (min(l16 + 16, q - 1) * a.n_pad + 4 * l4) * 8;
+      const Offset o0 = (Offset)((min(l16, q - 1) * a.n_pad + 4 * l4) * 8);
+      const Offset o1 = (Offset)((min(l16 + 16, q - 1) * a.n_pad + 4 * l4) * 8);
       for (int ch = ch_lo; ch < ch_hi; ++ch) {
         const int ns = (int)min((int64_t)kChunk, a.n - (int64_t)ch * kChunk);
         const char* qc = (const char*)(pd.Q + (int64_t)ch * kChunk);
@@ -1608,9 +1613,9 @@ __global__ __launch_bounds__(kRedoThreads) void redo_kernel(RedoArgs a) {
       double nw[kSlots / 4];
 #pragma unroll
       for (int kk = 0; kk < kSlots / 4; ++kk) nw[kk] = -w_s[4 * kk + l4][l16];
-      int64_t oq[kSlots / 4];
+      Offset oq[kSlots / 4];
 #pragma unroll
-      for (int kk = 0; kk < kSlots / 4; ++kk) oq[kk] = (min(4 * kk + l4, q - 1) * a.n_pad + l16) * 8;
+      for (int kk = 0; kk < kSlots / 4; ++kk) oq[kk] = (Offset)((min(4 * kk + l4, q - 1) * a.n_pad + l16) * 8);
       // the item's two 32-column blocks (columns past the panel's padded end
       // read the first block again; their results are not stored)
       constexpr int BB = block_bytes(PREC);
@@ -3253,13 +3258,19 @@ hipError_t launch_topk_read(const unsigned long long* words, int64_t n, int k, d
   return hipGetLastError();
 }
 
+template <bool FAR>
+static void (*redo_fn(int prec, bool g8))(RedoArgs) {
+  if (prec == kSplit8) return g8 ? redo_kernel<kSplit8, true, FAR> : redo_kernel<kSplit8, false, FAR>;
+  if (prec == kSplit16) return g8 ? redo_kernel<kSplit16, true, FAR> : redo_kernel<kSplit16, false, FAR>;
+  if (prec == kSplit && !g8) return redo_kernel<kSplit, false, FAR>;
+  if (prec == kFP32) return g8 ? redo_kernel<kFP32, true, FAR> : redo_kernel<kFP32, false, FAR>;
+  return nullptr;
+}
+
 hipError_t launch_redo(const RedoArgs& a, int grid, hipStream_t s) {
-  const bool g8 = a.code == 2;
-  void (*fn)(RedoArgs) = nullptr;
-  if (a.prec == kSplit8) fn = g8 ? redo_kernel<kSplit8, true> : redo_kernel<kSplit8, false>;
-  if (a.prec == kSplit16) fn = g8 ? redo_kernel<kSplit16, true> : redo_kernel<kSplit16, false>;
-  if (a.prec == kSplit && !g8) fn = redo_kernel<kSplit, false>;
-  if (a.prec == kFP32) fn = g8 ? redo_kernel<kFP32, true> : redo_kernel<kFP32, false>;
+  // 32-bit offsets reach the last of kSlots columns below 16.7 million samples
+  const bool far = (a.n_pad * kSlots) * 8 > (int64_t)UINT32_MAX;
+  void (*fn)(RedoArgs) = far ? redo_fn<true>(a.prec, a.code == 2) : redo_fn<false>(a.prec, a.code == 2);
   if (!fn) return hipErrorInvalidValue;
   hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kRedoThreads), 0, s, a);
   return hipGetLastError();
